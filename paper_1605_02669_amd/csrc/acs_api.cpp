@@ -46,7 +46,7 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Device buffers of one handle, as offsets into one allocation.
 struct Layout {
-  size_t xy, dist, crec, cand, eta, tau, tau2, etad, rpos, ctau, gvis, fpre, flim, femax, fbound, bflags, spm, spm_tail, xnn, gbox, gstart, gcnt, gcity, gxy, upd_rec, upd_nb, upd_next, upd_head, tours, lens,
+  size_t xy, dist, crec, cand, eta, tau, tau2, etad, rpos, ctau, gvis, fpre, flim, femax, fbound, bflags, spm, spm_tail, xnn, gstart, gcnt, gcity, gxy, upd_rec, upd_nb, upd_next, upd_head, tours, lens,
       best, gstate, counters, sync, dmax, lnn, total;
   size_t dist_rows;  // rows of the distance matrix `dist` holds at a time
 };
@@ -104,7 +104,6 @@ Layout make_layout(int n, int m, int cl, int ldn, int memory, int s, int mode) {
     L.spm_tail = take(sizeof(uint32_t) * (size_t)n);
     L.xnn = take(sizeof(uint32_t) * (size_t)n * std::min(acs::kXnn, n - 1));
     const size_t cells = (size_t)(grid_side(n) + 1) * (grid_side(n) + 1);
-    L.gbox = take(sizeof(double) * 4);
     L.gstart = take(sizeof(int32_t) * (cells + 1));
     L.gcnt = take(sizeof(int32_t) * cells);
     L.gcity = take(sizeof(uint32_t) * (size_t)n);
@@ -175,8 +174,10 @@ int check_params(int32_t n, const acs_params *p) {
 }
 
 // eta^beta for integer distance d (eta = 1/d; a zero distance reads as 1/2).
+// beta = 2 squares the integer, which is exact, as pow's result there is.
 float eta_beta(double beta, uint32_t d) {
   if (d == 0) return (float)std::pow(2.0, beta);
+  if (beta == 2.0) return (float)(1.0 / ((double)d * (double)d));
   return (float)(1.0 / std::pow((double)d, beta));
 }
 
@@ -243,71 +244,83 @@ int sync_and_check(acs_t *h) {
 
 int build(acs_t *h, const double *xy, float *eta_host) {
   const int n = h->n;
+  uint32_t *dmax_d = reinterpret_cast<uint32_t *>(h->ws + h->L.dmax);
+  int64_t *lnn_d = reinterpret_cast<int64_t *>(h->ws + h->L.lnn);
+  int32_t *cand = reinterpret_cast<int32_t *>(h->ws + h->L.cand);
+  const bool dense = h->p.memory == ACS_DENSE;
+  double x0 = xy[0], x1 = xy[0], y0 = xy[1], y1 = xy[1];  // bounding box
+  for (int i = 1; i < n; ++i) {
+    x0 = std::min(x0, xy[2 * i]);
+    x1 = std::max(x1, xy[2 * i]);
+    y0 = std::min(y0, xy[2 * i + 1]);
+    y1 = std::max(y1, xy[2 * i + 1]);
+  }
+  const double wx = x1 - x0, wy = y1 - y0, ext = std::max(wx, wy);
+  // two cities lie at least `ext` apart; below this no distance overflows the
+  // kernels' 32-bit integers, and the exact largest one is checked below
+  if (!(ext < 65536.0))
+    return fail(ACS_E_UNSUPPORTED, "largest distance (at least %g) exceeds 65535", ext);
   HIP_TRY(hipMemcpyAsync(h->ws + h->L.xy, xy, sizeof(double) * 2 * n, hipMemcpyHostToDevice,
                          h->stream));
   HIP_TRY(hipMemsetAsync(h->ws + h->L.dmax, 0, sizeof(uint32_t), h->stream));
-  uint32_t *dmax_d = reinterpret_cast<uint32_t *>(h->ws + h->L.dmax);
-  const bool dense = h->p.memory == ACS_DENSE;
-  // dense: the whole matrix; selective memory: only the largest distance
-  HIP_TRY(acs::launch_dist(h->dev, dmax_d, 0, n, dense, h->stream));
-  uint32_t dmax = 0;
-  HIP_TRY(hipMemcpyAsync(&dmax, dmax_d, sizeof dmax, hipMemcpyDeviceToHost, h->stream));
-  double box[4] = {0, 0, 0, 0};
-  if (!dense) {
-    double *box_d = reinterpret_cast<double *>(h->ws + h->L.gbox);
-    HIP_TRY(acs::launch_grid_box(h->dev, box_d, h->stream));
-    HIP_TRY(hipMemcpyAsync(box, box_d, sizeof box, hipMemcpyDeviceToHost, h->stream));
-  }
-  HIP_TRY(hipStreamSynchronize(h->stream));
-  if (dmax > 65535u)
-    return fail(ACS_E_UNSUPPORTED, "largest distance %u exceeds 65535", dmax);
-  if (!dense) {
+  if (dense) {
+    HIP_TRY(acs::launch_dist(h->dev, dmax_d, 0, n, h->stream));
+    HIP_TRY(acs::launch_near(h->dev, cand, dmax_d, 0, n, h->stream));
+  } else {
+    HIP_TRY(acs::launch_dmax(h->dev, dmax_d, h->stream));
     // square cells of side (largest extent) / side over the bounding box
     const int g = grid_side(n);
-    const double wx = box[2] - box[0], wy = box[3] - box[1];
-    const double ext = std::max(wx, wy);
     acs::Dev &dv = h->dev;
-    dv.gx0 = box[0];
-    dv.gy0 = box[1];
+    dv.gx0 = x0;
+    dv.gy0 = y0;
     dv.gh = ext > 0.0 ? ext / g : 1.0;
     dv.ginv = 1.0 / dv.gh;
     dv.gnx = std::min(g + 1, (int)std::floor(wx * dv.ginv) + 1);
     dv.gny = std::min(g + 1, (int)std::floor(wy * dv.ginv) + 1);
     HIP_TRY(acs::launch_grid(dv, reinterpret_cast<int32_t *>(h->ws + h->L.gcnt), h->stream));
-  }
-
-  int32_t *cand = reinterpret_cast<int32_t *>(h->ws + h->L.cand);
-  if (dense) {
-    HIP_TRY(acs::launch_cand(h->dev, cand, 0, n, h->stream));
-  } else {
     // the neighbour lists of the selective memory from chunks of distance
     // rows, computed in the region the tours take later
     const int rows = (int)h->L.dist_rows;
     for (int r0 = 0; r0 < n; r0 += rows) {
       const int nr = std::min(rows, n - r0);
-      HIP_TRY(acs::launch_dist(h->dev, dmax_d, r0, nr, true, h->stream));
-      HIP_TRY(acs::launch_cand(h->dev, cand, r0, nr, h->stream));
+      HIP_TRY(acs::launch_dist(h->dev, nullptr, r0, nr, h->stream));
+      HIP_TRY(acs::launch_near(h->dev, cand, dmax_d, r0, nr, h->stream));
     }
     h->dev.dist = nullptr;
   }
-  int64_t *lnn_d = reinterpret_cast<int64_t *>(h->ws + h->L.lnn);
-  HIP_TRY(acs::launch_nn_tour(h->dev, lnn_d, h->stream));
-  HIP_TRY(hipMemcpyAsync(&h->lnn, lnn_d, sizeof(int64_t), hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipStreamSynchronize(h->stream));
-  if (h->lnn <= 0) return fail(ACS_E_INVALID, "nearest-neighbour tour has length %lld",
-                               (long long)h->lnn);
+  // scratch for it: the dense pheromone, or the place of the tours, which holds
+  // at least 64 distance rows; neither is in use yet
+  HIP_TRY(acs::launch_nn_tour(h->dev, cand,
+                              reinterpret_cast<uint16_t *>(h->ws + (dense ? h->L.tau : h->L.tours)),
+                              lnn_d, h->stream));
 
   // Host constants of the method (scalars and the per-distance eta table).
+  // The table is made while the device works, up to the bounding box's
+  // diagonal (no distance is larger); the exact largest distance cuts it.
   const acs_params &p = h->p;
-  h->tau0 = p.tau0 > 0.0 ? (float)p.tau0 : (float)(1.0 / ((double)n * (double)h->lnn));
   std::vector<float> eta_vec;
   if (!eta_host) {
     eta_vec.resize(kEtaEntries);
     eta_host = eta_vec.data();
   }
   float *eta = eta_host;
-  std::fill(eta, eta + kEtaEntries, 0.f);
-  for (uint32_t d = 0; d <= dmax; ++d) eta[d] = eta_beta(p.beta, d);
+  const double diag = std::hypot(wx, wy) + 1.0;
+  const uint32_t top = diag < 65535.0 ? (uint32_t)diag + 1u : 65535u;
+  for (uint32_t d = 0; d <= top; ++d) eta[d] = eta_beta(p.beta, d);
+  uint32_t dmax = 0;
+  HIP_TRY(hipMemcpyAsync(&dmax, dmax_d, sizeof dmax, hipMemcpyDeviceToHost, h->stream));
+  HIP_TRY(hipMemcpyAsync(&h->lnn, lnn_d, sizeof(int64_t), hipMemcpyDeviceToHost, h->stream));
+  HIP_TRY(hipStreamSynchronize(h->stream));
+  if (dmax > 65535u)
+    return fail(ACS_E_UNSUPPORTED, "largest distance %u exceeds 65535", dmax);
+  if (dmax > top)
+    return fail(ACS_E_DEVICE, "largest distance %u exceeds the bounding box's %u", dmax, top);
+  if (h->lnn <= 0) return fail(ACS_E_INVALID, "nearest-neighbour tour has length %lld",
+                               (long long)h->lnn);
+
+  h->tau0 = p.tau0 > 0.0 ? (float)p.tau0 : (float)(1.0 / ((double)n * (double)h->lnn));
+  bool eta_falls = true;
+  for (uint32_t d = 0; d < dmax; ++d) eta_falls &= eta[d] >= eta[d + 1];
   if (p.memory == ACS_SPM) {
     // the selective memory's fallback relies on tau0 * eta^beta(d) strictly
     // decreasing in d (every trail outside a record holds tau0)
@@ -316,10 +329,10 @@ int build(acs_t *h, const double *xy, float *eta_host) {
         return fail(ACS_E_UNSUPPORTED,
                     "tau0 * eta^beta is not strictly decreasing at d = %u (selective memory)", d);
   }
-  HIP_TRY(hipMemcpyAsync(h->ws + h->L.eta, eta, sizeof(float) * kEtaEntries,
+  HIP_TRY(hipMemcpyAsync(h->ws + h->L.eta, eta, sizeof(float) * ((size_t)dmax + 1),
                          hipMemcpyHostToDevice, h->stream));
   HIP_TRY(acs::launch_crec(h->dev, cand, h->tau0, h->stream));
-  HIP_TRY(acs::launch_init_pheromone(h->dev, h->tau0, h->stream));
+  HIP_TRY(acs::launch_fill(h->dev, h->tau0, dmax, eta_falls, h->stream));
   HIP_TRY(hipStreamSynchronize(h->stream));
 
   acs::Iter &b = h->base;

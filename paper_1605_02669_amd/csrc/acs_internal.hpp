@@ -91,21 +91,26 @@ struct Iter {
 };
 
 // ---- instance preparation ----
-// Distances of rows r0 .. r0 + rows - 1 (stored from the start of d.dist
-// when `store`) and their largest value into *dmax.
-hipError_t launch_dist(const Dev &d, uint32_t *dmax, int r0, int rows, bool store,
+// Distances of rows r0 .. r0 + rows - 1, stored from the start of d.dist, and
+// (dmax not null) their largest value into *dmax.
+hipError_t launch_dist(const Dev &d, uint32_t *dmax, int r0, int rows, hipStream_t s);
+// The largest distance of the instance into *dmax, from the coordinates.
+hipError_t launch_dmax(const Dev &d, uint32_t *dmax, hipStream_t s);
+// Nearest cities of r0 .. r0 + rows - 1 from the distance rows d.dist holds:
+// candidate lists and, beyond them, the dense fallback's prefix or the
+// selective memory's extended lists.  *dmax: the largest distance.
+hipError_t launch_near(const Dev &d, int32_t *cand_tmp, const uint32_t *dmax, int r0, int rows,
                        hipStream_t s);
-// Candidate lists (and, with the selective memory, the extended neighbour
-// lists) of cities r0 .. r0 + rows - 1 from the distance rows d.dist holds.
-hipError_t launch_cand(const Dev &d, int32_t *cand_tmp, int r0, int rows, hipStream_t s);
-hipError_t launch_nn_tour(const Dev &d, int64_t *lnn_out, hipStream_t s);
-// Bounding box of the cities into box[0..3] = {xmin, ymin, xmax, ymax}.
-hipError_t launch_grid_box(const Dev &d, double *box, hipStream_t s);
+// L_nn from the lists of launch_near; d.best and near (n x 16) are scratch.
+hipError_t launch_nn_tour(const Dev &d, const int32_t *cand_tmp, uint16_t *near, int64_t *lnn_out,
+                          hipStream_t s);
 // The grid's cell lists (d.gnx, d.gny, d.gx0, d.gy0, d.ginv set): counts,
 // starts, then the cities in cell order; cnt: gnx * gny ints of scratch.
 hipError_t launch_grid(const Dev &d, int32_t *cnt, hipStream_t s);
 hipError_t launch_crec(const Dev &d, const int32_t *cand_tmp, float tau0, hipStream_t s);
-hipError_t launch_init_pheromone(const Dev &d, float tau0, hipStream_t s);
+// Initial pheromone, eta^beta of every entry and of the prefix, counters and
+// state.  eta_falls: the table never grows with the distance (up to dmax).
+hipError_t launch_fill(const Dev &d, float tau0, uint32_t dmax, bool eta_falls, hipStream_t s);
 
 // ---- one iteration ----
 // Construction of all m tours.  mode 0 = synchronous steps (cooperative

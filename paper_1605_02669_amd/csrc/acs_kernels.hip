@@ -52,16 +52,20 @@ __device__ __forceinline__ uint4 philox10(uint4 c, uint32_t k0, uint32_t k1) {
 
 // Cost d_ij (Sec. 3) as TSPLIB EUC_2D made exact: s = dx*dx + dy*dy in
 // double, d = the integer with (d - 1/2)^2 <= s < (d + 1/2)^2 (0 if s < 1/4).
-// The square root only seeds the search; the result is set by exact compares.
+// A handle's coordinates span less than 65536 each way, so sqrt(s) < 92682 and
+// its fp32 approximation (the rounding of s and one ulp) is off by less than
+// 0.02: its integer part is d, or d - 1 where sqrt(s) lies in the upper half
+// before d or just above d, and one exact compare decides.
+__device__ __forceinline__ uint32_t dist_of_square(double s) {
+  const uint32_t d = (uint32_t)__builtin_amdgcn_sqrtf((float)s);
+  const double h = d + 0.5;
+  return d + (h * h <= s ? 1u : 0u);
+}
+
 __device__ __forceinline__ uint32_t exact_dist(double xi, double yi, double xj,
                                                double yj) {
   const double dx = xi - xj, dy = yi - yj;
-  const double s = dx * dx + dy * dy;
-  if (s < 0.25) return 0;
-  uint32_t d = (uint32_t)sqrt(s);
-  while ((d + 0.5) * (d + 0.5) <= s) ++d;
-  while (d > 0 && (d - 0.5) * (d - 0.5) > s) --d;
-  return d;
+  return dist_of_square(dx * dx + dy * dy);
 }
 
 // d(i, j) from the coordinates (the selective memory keeps no n x n matrix).
@@ -289,103 +293,196 @@ __device__ __forceinline__ void grid_barrier_f(const Dev &D, uint64_t epoch) {
 // ---------------------------------------------------------------------------
 // Instance preparation kernels.
 // ---------------------------------------------------------------------------
-// Rows r0 .. r0 + rows - 1 of the distance matrix, stored (when `store`)
-// from the start of D.dist, and the largest distance into *dmax.
-__global__ __launch_bounds__(256) void k_dist(Dev D, uint32_t *dmax, int r0, int rows,
-                                              int store) {
-  const int j = blockIdx.x * 64 + (threadIdx.x & 63);
+// Largest value of a block's lanes into *word.  The block reduces it in LDS
+// first and skips the atomic when the word already holds as much: one atomic
+// per wave on one address took 12.9 ms per 2 * 10^8 distances, about all of
+// the kernel's time.
+__device__ __forceinline__ void block_max_into(uint32_t v, uint32_t *word) {
+  __shared__ uint32_t sm[16];
+  v = wave_umax_u(v);
+  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) v = max(v, sm[w]);
+    if (v > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(word, v);
+  }
+}
+
+// Rows r0 .. r0 + rows - 1 of the distance matrix, stored from the start of
+// D.dist, and (dmax not null) the largest distance into *dmax.  A wave takes
+// 512 columns of a row, eight per lane and one 16-byte store.
+__global__ __launch_bounds__(256) void k_dist(Dev D, uint32_t *dmax, int r0, int rows) {
+  const int j0 = 8 * (blockIdx.x * 64 + (threadIdx.x & 63));
   const int r = blockIdx.y * 4 + (threadIdx.x >> 6);
   const int i = r0 + r;
-  uint32_t d = 0;
-  if (r < rows && i < D.n && j < D.n && i != j) d = dist_xy(D, i, j);
-  const uint32_t wmax = wave_max(d);
-  if ((threadIdx.x & 63) == 0 && wmax) atomicMax(dmax, wmax);
-  if (store && r < rows && i < D.n && j < D.ldn)
-    const_cast<uint16_t *>(D.dist)[(size_t)r * D.ldn + j] = (uint16_t)(d > 65535u ? 65535u : d);
+  uint32_t mx = 0;
+  if (r < rows && i < D.n && j0 < D.ldn) {
+    const double xi = D.xy[2 * i], yi = D.xy[2 * i + 1];
+    const double2 *c = reinterpret_cast<const double2 *>(D.xy);
+    uint32_t w[4];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int j = j0 + q;
+      const double2 p = c[min(j, D.n - 1)];
+      uint32_t d = j < D.n && j != i ? exact_dist(xi, yi, p.x, p.y) : 0u;
+      mx = max(mx, d);
+      d = min(d, 65535u);
+      w[q >> 1] = q & 1 ? w[q >> 1] | d << 16 : d;
+    }
+    *reinterpret_cast<uint4 *>(const_cast<uint16_t *>(D.dist) + (size_t)r * D.ldn + j0) =
+        make_uint4(w[0], w[1], w[2], w[3]);
+  }
+  if (dmax) block_max_into(mx, dmax);
 }
 
-// Candidate list of city i: its cl nearest neighbours by (d, j), one wave
-// per city, extracted in increasing order of the key (d << 16 | j).
-// Cities r0 .. r0 + rows - 1, whose distance rows D.dist holds from its start.
-__global__ __launch_bounds__(256) void k_cand(Dev D, int32_t *cand, int r0, int rows) {
-  const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int i = r0 + r;
-  if (r >= rows || i >= D.n) return;
-  const uint16_t *row = D.dist + (size_t)r * D.ldn;
-  int64_t last = -1;
-  for (int k = 0; k < D.cl; ++k) {
-    int64_t best = INT64_MAX;
-    for (int j = lane; j < D.n; j += 64) {
-      if (j == i) continue;
-      const int64_t key = ((int64_t)row[j] << 16) | j;
-      if (key > last && key < best) best = key;
-    }
-    best = wave_min(best);
-    if (lane == 0) cand[(size_t)i * D.cl + k] = (int32_t)(best & 0xffff);
-    last = best;
+// The largest distance of the instance without a matrix (selective memory):
+// distances grow with their squares, so each thread keeps the largest square
+// of its city against kDmaxRows others (read through the scalar cache) and
+// takes one root.  Pairs are covered once, from the smaller index's side.
+constexpr int kDmaxRows = 256;
+__global__ __launch_bounds__(256) void k_dmax(Dev D, uint32_t *dmax) {
+  const int j = blockIdx.x * 256 + threadIdx.x;
+  const int i0 = blockIdx.y * kDmaxRows;
+  if (i0 > (int)(blockIdx.x * 256 + 255)) return;  // the whole block: no i < j
+  const double2 *c = reinterpret_cast<const double2 *>(D.xy);
+  const double2 p = c[min(j, D.n - 1)];
+  const int i1 = min(i0 + kDmaxRows, D.n);
+  double s = 0.0;
+  for (int i = i0; i < i1; ++i) {
+    const double dx = p.x - c[i].x, dy = p.y - c[i].y;
+    s = fmax(s, dx * dx + dy * dy);
+  }
+  block_max_into(dist_of_square(s), dmax);
+}
+
+// The nearest cities of city r0 + blockIdx.x by (d, j), from its row of
+// distances (D.dist holds rows r0 .. from its start): the cl candidates, and
+// beyond them the fallback's prefix with the key of the city after it (dense;
+// the eta^beta words follow with k_fill) or the extended list (selective
+// memory).  One block per city: a histogram of the distances (1024 bins over
+// the instance's range, refined to single distances when the bin of the K-th
+// city is crowded) gives a threshold, the cities within it are gathered into
+// LDS and each finds its rank among them.  Three passes over the row replace
+// one pass per listed city, which took 13.7 ms for 2048 rows of n = 20000
+// (now 0.031 ms) and 1.3 ms for all rows of n = 2392 (now 0.017 ms).
+constexpr int kNearBins = 1024, kNearCap = 512;
+
+__device__ __forceinline__ void near_emit(const Dev &D, int32_t *cand, int i, int rank,
+                                          uint32_t key) {
+  if (rank < D.cl) cand[(size_t)i * D.cl + rank] = (int32_t)(key & 0xffffu);
+  if (D.xnn && rank < D.xl) const_cast<uint32_t *>(D.xnn)[(size_t)i * D.xl + rank] = key;
+  if (D.fpre) {
+    const int p = rank - D.cl;
+    uint32_t *out = reinterpret_cast<uint32_t *>(const_cast<uint4 *>(D.fpre)) +
+                    (size_t)i * 2 * kFpre;
+    if (p >= 0 && p < kFpre) out[2 * p] = key;
+    if (p == kFpre) const_cast<uint32_t *>(D.flim)[i] = key;
   }
 }
 
-// The xl nearest cities of every city by (d, j) (selective memory only),
-// each stored as its key d << 16 | j: the fallback's nearest unvisited city
-// is usually among them.  Cities r0 .. r0 + rows - 1, as k_cand.
-__global__ __launch_bounds__(256) void k_xnn(Dev D, int r0, int rows) {
-  const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int i = r0 + r;
-  if (r >= rows || i >= D.n) return;
-  const uint16_t *row = D.dist + (size_t)r * D.ldn;
-  int64_t last = -1;
-  for (int k = 0; k < D.xl; ++k) {
-    int64_t best = INT64_MAX;
-    for (int j = lane; j < D.n; j += 64) {
-      if (j == i) continue;
-      const int64_t key = ((int64_t)row[j] << 16) | j;
-      if (key > last && key < best) best = key;
-    }
-    best = wave_min(best);
-    if (lane == 0) const_cast<uint32_t *>(D.xnn)[(size_t)i * D.xl + k] = (uint32_t)best;
-    last = best;
-  }
-}
+__global__ __launch_bounds__(256) void k_near(Dev D, int32_t *cand, const uint32_t *dmax, int r0) {
+  __shared__ uint32_t hist[kNearBins];
+  __shared__ alignas(16) uint32_t keys[kNearCap];
+  __shared__ uint32_t wsum[4], s_bin, s_before, s_count, s_fill;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int i = r0 + blockIdx.x, n = D.n;
+  const uint16_t *row = D.dist + (size_t)blockIdx.x * D.ldn;
+  const uint32_t K = (uint32_t)(D.fpre ? D.cl + kFpre + 1 : D.xnn ? max(D.cl, D.xl) : D.cl);
+  const uint32_t dm = min(*dmax, 65535u);
+  const int S = max(0, 22 - (int)__clz((int)max(dm, 1u)));  // dm >> S < 1024
 
-// The dense fallback's prefix of city i: positions cl .. cl + kFpre - 1 of
-// its neighbours in (d, j) order (the candidates are positions 0 .. cl - 1),
-// the key of position cl + kFpre, and the largest eta^beta of the cities
-// from that position on (eta^beta need not be monotone in fp32).
-__global__ __launch_bounds__(256) void k_fpre(Dev D) {
-  const int lane = threadIdx.x & 63;
-  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= D.n) return;
-  const uint16_t *row = D.dist + (size_t)i * D.ldn;
-  uint32_t *out = reinterpret_cast<uint32_t *>(const_cast<uint4 *>(D.fpre)) +
-                  (size_t)i * 2 * kFpre;
-  const int P = D.cl + kFpre;
-  int64_t last = -1;
-  for (int k = 0; k <= P; ++k) {
-    int64_t best = INT64_MAX;
-    for (int j = lane; j < D.n; j += 64) {
-      if (j == i) continue;
-      const int64_t key = ((int64_t)row[j] << 16) | j;
-      if (key > last && key < best) best = key;
+  auto each = [&](auto f) {  // f(d, j) over the row's other cities
+    for (int j0 = 8 * tid; j0 < n; j0 += 2048) {
+      const uint4 v = *reinterpret_cast<const uint4 *>(row + j0);
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int j = j0 + q;
+        if (j < n && j != i) f((w[q >> 1] >> (16 * (q & 1))) & 0xffffu, (uint32_t)j);
+      }
     }
-    best = wave_min(best);
-    if (lane == 0 && k >= D.cl && k < P) {
-      const uint32_t d = (uint32_t)(best >> 16), j = (uint32_t)(best & 0xffff);
-      out[2 * (k - D.cl)] = j | d << 16;
-      out[2 * (k - D.cl) + 1] = __float_as_uint(D.eta_tab[d]);
+  };
+  // the bin where the running count from `before` reaches K: s_bin, the
+  // count below it s_before and through it s_count
+  auto find = [&](uint32_t before) {
+    uint32_t h[4], sum = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum += h[q] = hist[4 * tid + q];
+    uint32_t inc = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t o = (uint32_t)__shfl_up((int)inc, off, 64);
+      if (lane >= off) inc += o;
     }
-    if (lane == 0 && k == P) const_cast<uint32_t *>(D.flim)[i] = (uint32_t)best;
-    last = best;
+    if (lane == 63) wsum[wv] = inc;
+    __syncthreads();
+    uint32_t run = before + inc - sum;
+    for (int w = 0; w < wv; ++w) run += wsum[w];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (run < K && run + h[q] >= K) {
+        s_bin = (uint32_t)(4 * tid + q);
+        s_before = run;
+        s_count = run + h[q];
+      }
+      run += h[q];
+    }
+    __syncthreads();
+  };
+
+  for (int b = tid; b < kNearBins; b += 256) hist[b] = 0u;
+  if (tid == 0) s_fill = 0u;
+  __syncthreads();
+  each([&](uint32_t d, uint32_t) { atomicAdd(&hist[d >> S], 1u); });
+  __syncthreads();
+  find(0u);
+  uint32_t limit = ((s_bin + 1) << S) - 1u, count = s_count;
+  if (count > (uint32_t)kNearCap && S > 0) {
+    const uint32_t bin = s_bin, before = s_before;
+    __syncthreads();
+    for (int b = tid; b < kNearBins; b += 256) hist[b] = 0u;
+    __syncthreads();
+    each([&](uint32_t d, uint32_t) {
+      if (d >> S == bin) atomicAdd(&hist[d & ((1u << S) - 1u)], 1u);
+    });
+    __syncthreads();
+    find(before);
+    limit = (bin << S) + s_bin;
+    count = s_count;
   }
-  uint32_t emax = 0;
-  for (int j = lane; j < D.n; j += 64) {
-    const uint32_t key = (uint32_t)row[j] << 16 | (uint32_t)j;
-    if (j != i && (int64_t)key >= last) emax = max(emax, __float_as_uint(D.eta_tab[row[j]]));
+  if (count > (uint32_t)kNearCap) {
+    // hundreds of cities at one distance: one pass per listed city
+    if (wv > 0) return;
+    int64_t last = -1;
+    for (uint32_t k = 0; k < K; ++k) {
+      int64_t best = INT64_MAX;
+      for (int j = lane; j < n; j += 64) {
+        if (j == i) continue;
+        const int64_t key = ((int64_t)row[j] << 16) | j;
+        if (key > last && key < best) best = key;
+      }
+      best = wave_min(best);
+      if (lane == 0) near_emit(D, cand, i, (int)k, (uint32_t)best);
+      last = best;
+    }
+    return;
   }
-  emax = wave_umax_u(emax);
-  if (lane == 0) const_cast<float *>(D.femax)[i] = __uint_as_float(emax);
+  each([&](uint32_t d, uint32_t j) {
+    if (d <= limit) keys[atomicAdd(&s_fill, 1u)] = d << 16 | j;
+  });
+  __syncthreads();
+  if (tid < 4 && count + tid < (uint32_t)kNearCap) keys[count + tid] = kNone;
+  __syncthreads();
+  for (uint32_t u = tid; u < count; u += 256) {
+    const uint32_t key = keys[u];
+    uint32_t rank = 0;
+    for (uint32_t v = 0; v < count; v += 4) {
+      const uint4 o = *reinterpret_cast<const uint4 *>(keys + v);
+      rank += (o.x < key) + (o.y < key) + (o.z < key) + (o.w < key);
+    }
+    if (rank < K) near_emit(D, cand, i, (int)rank, key);
+  }
 }
 
 // Uniform grid over the cities (selective memory): the fallback's search
@@ -396,36 +493,6 @@ __device__ __forceinline__ int grid_cx(const Dev &D, double x) {
 }
 __device__ __forceinline__ int grid_cy(const Dev &D, double y) {
   return min(max((int)((y - D.gy0) * D.ginv), 0), D.gny - 1);
-}
-
-// Bounding box, one block of 1024 threads.
-__global__ __launch_bounds__(1024) void k_grid_box(Dev D, double *box) {
-  __shared__ double sm[4][16];
-  double v[4] = {INFINITY, INFINITY, -INFINITY, -INFINITY};
-  for (int j = threadIdx.x; j < D.n; j += 1024) {
-    const double x = D.xy[2 * j], y = D.xy[2 * j + 1];
-    v[0] = fmin(v[0], x);
-    v[1] = fmin(v[1], y);
-    v[2] = fmax(v[2], x);
-    v[3] = fmax(v[3], y);
-  }
-#pragma unroll
-  for (int off = 32; off; off >>= 1) {
-    v[0] = fmin(v[0], __shfl_xor(v[0], off, 64));
-    v[1] = fmin(v[1], __shfl_xor(v[1], off, 64));
-    v[2] = fmax(v[2], __shfl_xor(v[2], off, 64));
-    v[3] = fmax(v[3], __shfl_xor(v[3], off, 64));
-  }
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
-    for (int q = 0; q < 4; ++q) sm[q][w] = v[q];
-  __syncthreads();
-  if (threadIdx.x < 4) {
-    double r = sm[threadIdx.x][0];
-    for (int i = 1; i < 16; ++i)
-      r = threadIdx.x < 2 ? fmin(r, sm[threadIdx.x][i]) : fmax(r, sm[threadIdx.x][i]);
-    box[threadIdx.x] = r;
-  }
 }
 
 __global__ __launch_bounds__(256) void k_grid_count(Dev D, int32_t *cnt) {
@@ -477,62 +544,163 @@ __global__ __launch_bounds__(256) void k_grid_fill(Dev D, int32_t *cur) {
 }
 
 // Nearest-neighbour tour from city 0 (ties: lowest index), one block; its
-// length L_nn defines tau0 = 1 / (n * L_nn).
-__global__ __launch_bounds__(1024) void k_nn_tour(Dev D, int64_t *lnn) {
+// length L_nn defines tau0 = 1 / (n * L_nn).  A chain of n - 1 dependent
+// choices, so what counts is one choice's latency: the first C neighbours of
+// every city sit in LDS as 16-bit indices (as many of 16 as fit) and the first
+// wave follows them alone, with LDS operations only and one store per 64
+// cities.  Where they are all visited, it reads the first 16 from `near`
+// (16-bit, n x 16, where C < 16: this block writes it first, so it comes from
+// its L2), then the city's stored list (the candidates and the prefix, or the
+// extended list), and only when that is used up too does the whole block scan
+// every city.  The lists are sorted by (d, j), so the first unvisited city of
+// one is the answer.  The order is left in D.best (not in use yet) and summed
+// at the end by all threads.  With a block barrier and a row scan or a list
+// read per choice, n = 2392 took 5.6 ms and n = 20000 14.1 ms; this takes
+// 0.40 and 6.3 ms (0.16 us a choice).
+constexpr int kNnList = 16;
+template <bool NEAR>
+__global__ __launch_bounds__(1024) void k_nn_tour(Dev D, const int32_t *cand, int C,
+                                                  uint16_t *near, int64_t *lnn) {
+  extern __shared__ uint16_t lst[];  // n x C
   __shared__ uint32_t vis[2048];
   __shared__ int64_t red[16];
-  const int tid = threadIdx.x;
-  const int W = (D.n + 31) >> 5;
+  __shared__ int s_cur, s_step;
+  const int tid = threadIdx.x, lane = tid & 63, n = D.n, cl = D.cl;
+  const int have = D.xnn ? D.xl : cl;
+  const int W = (n + 31) >> 5;
+  auto listed = [&](int c, int k) {
+    return D.xnn ? D.xnn[(size_t)c * D.xl + k] & 0xffffu : (uint32_t)cand[(size_t)c * cl + k];
+  };
   for (int w = tid; w < W; w += 1024) vis[w] = 0;
-  __syncthreads();
-  if (tid == 0) vis[0] = 1u;
-  __shared__ int64_t listed;
-  int cur = 0;
-  int64_t L = 0;
-  for (int step = 1; step < D.n; ++step) {
-    __syncthreads();
-    // without a distance matrix: the first unvisited city of cur's list of
-    // nearest cities (sorted by (d, j)) is the answer when there is one
-    if (!D.dist && tid < 64) {
-      int64_t key = -1;
-      const uint32_t *xr = D.xnn + (size_t)cur * D.xl;
-      for (int b0 = 0; b0 < D.xl; b0 += 64) {
-        const int idx = b0 + tid;
-        const uint32_t e = idx < D.xl ? xr[idx] : 0u;
-        const uint32_t j = e & 0xffffu;
-        const uint64_t ok = __ballot(idx < D.xl && !((vis[j >> 5] >> (j & 31)) & 1u));
-        if (ok) {
-          key = (int64_t)rdlane(e, (int)__ffsll((unsigned long long)ok) - 1);
-          break;
-        }
-      }
-      if (tid == 0) listed = key;
-    }
-    __syncthreads();
-    int64_t best = D.dist ? -1 : listed;
-    if (best < 0) {
-      best = INT64_MAX;
-      for (int j = tid; j < D.n; j += 1024)
-        if (!((vis[j >> 5] >> (j & 31)) & 1u)) {
-          const uint32_t dj = D.dist ? D.dist[(size_t)cur * D.ldn + j] : dist_xy(D, cur, j);
-          const int64_t key = ((int64_t)dj << 16) | j;
-          best = key < best ? key : best;
-        }
-      best = wave_min(best);
-      if ((tid & 63) == 0) red[tid >> 6] = best;
-      __syncthreads();
-      best = red[0];
-      for (int w = 1; w < 16; ++w) best = red[w] < best ? red[w] : best;
-    }
-    const int nxt = (int)(best & 0xffff);
-    L += best >> 16;
-    if (tid == 0) vis[nxt >> 5] |= 1u << (nxt & 31);
-    cur = nxt;
+  const int nl = min(kNnList, have);
+  for (int e = tid; e < n * kNnList; e += 1024) {
+    const int c = e / kNnList, k = e % kNnList;
+    if (k >= nl) continue;
+    const uint32_t j = listed(c, k);
+    if (k < C) lst[c * C + k] = (uint16_t)j;
+    if (NEAR) near[e] = (uint16_t)j;
   }
-  if (tid == 0) *lnn = L + (D.dist ? D.dist[(size_t)cur * D.ldn] : dist_xy(D, cur, 0));
+  __threadfence_block();
+  __syncthreads();
+  if (tid == 0) {
+    vis[0] = 1u;
+    s_cur = 0;
+    s_step = 1;
+  }
+  __syncthreads();
+  // lanes whose city j is unvisited
+  auto open = [&](uint32_t j) -> uint64_t {
+    return __ballot(((vis[j >> 5] >> (j & 31)) & 1u) == 0);
+  };
+  auto low = [](uint64_t m) { return (int)__ffsll((unsigned long long)m) - 1; };
+  int buf = 0;  // the first wave's order, entry t on lane t % 64 (entry 0: city 0)
+  while (true) {
+    if (tid < 64) {
+      int cur = uni(s_cur), t = uni(s_step);
+      const int kc = min(lane, C - 1), kn = min(lane, nl - 1);
+      const uint64_t mc = ~0ull >> (64 - C), mn = ~0ull >> (64 - nl);
+      while (t < n) {
+        // up to the next 64-boundary, by the lists in LDS (and L2)
+        const int tend = min(n, (t | 63) + 1);
+        bool out = false;
+        do {
+          const uint32_t j2 = NEAR ? near[cur * kNnList + kn] : 0u;
+          const uint32_t j1 = lst[cur * C + kc];
+          uint32_t j = j1;
+          uint64_t ok = open(j1) & mc;
+          if (NEAR && !ok) {
+            j = j2;
+            ok = open(j2) & mn;
+          }
+          if (!ok) {
+            out = true;
+            break;
+          }
+          const int k = low(ok);
+          cur = (int)rdlane(j, k);
+          // lane k marks its city, the others OR zeros
+          __hip_atomic_fetch_or(vis + (j >> 5), lane == k ? 1u << (j & 31) : 0u,
+                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          buf = (int)wrlane((uint32_t)cur, t & 63, (uint32_t)buf);
+        } while (++t < tend);
+        if (out) {
+          int nxt = -1;
+          for (int b0 = C; nxt < 0 && b0 < have; b0 += 64) {
+            const uint32_t j = listed(cur, min(b0 + lane, have - 1));
+            const uint64_t ok = open(j) & (have - b0 >= 64 ? ~0ull : ~(~0ull << (have - b0)));
+            if (ok) nxt = (int)rdlane(j, low(ok));
+          }
+          if (nxt < 0 && D.fpre) {
+            // lane l holds the prefix positions 2l and 2l + 1
+            const uint4 pe = D.fpre[(size_t)cur * (kFpre / 2) + lane];
+            const uint32_t j0 = pe.x & 0xffffu, j1 = pe.z & 0xffffu;
+            const uint64_t o0 = open(j0), o1 = open(j1);
+            if (o0 | o1) {
+              const int k = low(o0 | o1);
+              nxt = (int)rdlane((o0 >> lane) & 1u ? j0 : j1, k);
+            }
+          }
+          if (nxt < 0) break;
+          if (lane == 0) mark(vis, nxt);
+          buf = (int)wrlane((uint32_t)nxt, t & 63, (uint32_t)buf);
+          cur = nxt;
+          ++t;
+        }
+        if ((t & 63) == 0) D.best[t - 64 + lane] = buf;
+      }
+      if (tid == 0) {
+        s_cur = cur;
+        s_step = t;
+      }
+    }
+    __syncthreads();
+    const int cur = s_cur, t = s_step;
+    if (t >= n) break;
+    int64_t best = INT64_MAX;
+    for (int j = tid; j < n; j += 1024)
+      if (!((vis[j >> 5] >> (j & 31)) & 1u)) {
+        const uint32_t dj = D.dist ? D.dist[(size_t)cur * D.ldn + j] : dist_xy(D, cur, j);
+        const int64_t key = ((int64_t)dj << 16) | j;
+        best = key < best ? key : best;
+      }
+    best = wave_min(best);
+    if (lane == 0) red[tid >> 6] = best;
+    __syncthreads();
+    if (tid < 64) {
+      best = red[lane & 15];
+      best = wave_min(best);
+      const int nxt = (int)(best & 0xffff);
+      buf = lane == (t & 63) ? nxt : buf;
+      if (((t + 1) & 63) == 0) D.best[t - 63 + lane] = buf;
+      if (tid == 0) {
+        mark(vis, nxt);
+        s_cur = nxt;
+        s_step = t + 1;
+      }
+    }
+    __syncthreads();
+  }
+  if (tid < (n & 63)) D.best[(n & ~63) + tid] = buf;
+  // the order's stores are this block's own: visible after a fence
+  __threadfence_block();
+  __syncthreads();
+  int64_t L = 0;
+  for (int p = tid; p < n; p += 1024)
+    L += dist_xy(D, D.best[p], D.best[p + 1 < n ? p + 1 : 0]);
+#pragma unroll
+  for (int off = 32; off; off >>= 1) L += __shfl_xor(L, off, 64);
+  if (lane == 0) red[tid >> 6] = L;
+  __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < 16; ++w) L += red[w];
+    *lnn = L;
+  }
 }
 
-// Candidate records with the initial pheromone tau0 in the last word.
+// Candidate records with the initial pheromone tau0 in the last word, and
+// (dense memory) the reverse positions: for candidate k of city i (j =
+// cand[i][k]), the position of i in j's candidate list, -1 if i is not a
+// candidate of j.
 __global__ __launch_bounds__(256) void k_crec(Dev D, const int32_t *cand, float tau0) {
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= D.n * D.cl) return;
@@ -541,26 +709,10 @@ __global__ __launch_bounds__(256) void k_crec(Dev D, const int32_t *cand, float 
   const uint32_t d = dist_xy(D, i, (int)c);
   const_cast<uint4 *>(D.crec)[e] =
       make_uint4(c, d, __float_as_uint(D.eta_tab[d]), __float_as_uint(tau0));
-}
-
-// eta^beta of every entry (dense memory): one load per city in the fallback
-// scan instead of a distance load followed by a table lookup.
-__global__ __launch_bounds__(256) void k_etad(Dev D) {
-  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= (size_t)D.n * D.ldn) return;
-  const_cast<float *>(D.etad)[e] = D.eta_tab[D.dist[e]];
-}
-
-// Reverse positions: for candidate k of city i (j = cand[i][k]), the position
-// of i in j's candidate list, -1 if i is not a candidate of j.
-__global__ __launch_bounds__(256) void k_rpos(Dev D) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= D.n * D.cl) return;
-  const int i = e / D.cl;
-  const uint32_t j = D.crec[e].x;
+  if (!D.rpos) return;
   int r = -1;
   for (int k = 0; k < D.cl && r < 0; ++k)
-    if (D.crec[(size_t)j * D.cl + k].x == (uint32_t)i) r = k;
+    if (cand[(size_t)c * D.cl + k] == i) r = k;
   const_cast<int8_t *>(D.rpos)[e] = (int8_t)r;
 }
 
@@ -658,10 +810,31 @@ __global__ __launch_bounds__(256) void k_ctau_out_batch(const Dev *devs, int can
   if (e < (size_t)D.n * D.cl) ctau_out_slot(D, e, canonical != 0);
 }
 
-__global__ __launch_bounds__(256) void k_init(Dev D, float tau0) {
+// The initial pheromone and everything else that needs only the eta^beta
+// table: eta^beta of every entry (dense memory: one load per city in the
+// fallback scan instead of a distance load followed by a table lookup), the
+// prefix's eta^beta words and, per city, the largest eta^beta from the city
+// after the prefix on.  That is the eta^beta of this city's distance where
+// the table never grows with the distance (eta_falls); else it is taken over
+// the table from there to the largest distance.
+__global__ __launch_bounds__(256) void k_fill(Dev D, float tau0, uint32_t dmax, int eta_falls) {
   const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
   const size_t nd = (size_t)D.n * D.ldn;
-  if (D.tau && e < nd) D.tau[e] = tau0;
+  if (D.tau && e < nd) {
+    D.tau[e] = tau0;
+    const_cast<float *>(D.etad)[e] = D.eta_tab[D.dist[e]];
+  }
+  if (D.fpre && e < (size_t)D.n * kFpre) {
+    uint32_t *w = reinterpret_cast<uint32_t *>(const_cast<uint4 *>(D.fpre)) + 2 * e;
+    w[1] = __float_as_uint(D.eta_tab[w[0] >> 16]);
+  }
+  if (D.fpre && e < (size_t)D.n) {
+    const uint32_t d = D.flim[e] >> 16;
+    float mx = D.eta_tab[d];
+    if (!eta_falls)
+      for (uint32_t x = d + 1; x <= dmax; ++x) mx = fmaxf(mx, D.eta_tab[x]);
+    const_cast<float *>(D.femax)[e] = mx;
+  }
   if (D.spm && e < (size_t)D.n * D.spm_s) D.spm[e] = make_uint2(kNone, __float_as_uint(tau0));
   if (D.spm_tail && e < (size_t)D.n) {
     D.spm_tail[e] = (uint32_t)(D.spm_s - 1);
@@ -3485,15 +3658,15 @@ constexpr int kAsyncBlock = 256;
 // ---------------------------------------------------------------------------
 // Launch wrappers.
 // ---------------------------------------------------------------------------
-hipError_t launch_dist(const Dev &d, uint32_t *dmax, int r0, int rows, bool store,
-                       hipStream_t s) {
-  dim3 grid((d.ldn + 63) / 64, (rows + 3) / 4);
-  hipLaunchKernelGGL(k_dist, grid, dim3(256), 0, s, d, dmax, r0, rows, store ? 1 : 0);
+hipError_t launch_dist(const Dev &d, uint32_t *dmax, int r0, int rows, hipStream_t s) {
+  dim3 grid((d.ldn + 511) / 512, (rows + 3) / 4);
+  hipLaunchKernelGGL(k_dist, grid, dim3(256), 0, s, d, dmax, r0, rows);
   return hipGetLastError();
 }
 
-hipError_t launch_grid_box(const Dev &d, double *box, hipStream_t s) {
-  hipLaunchKernelGGL(k_grid_box, dim3(1), dim3(1024), 0, s, d, box);
+hipError_t launch_dmax(const Dev &d, uint32_t *dmax, hipStream_t s) {
+  dim3 grid((d.n + 255) / 256, (d.n + kDmaxRows - 1) / kDmaxRows);
+  hipLaunchKernelGGL(k_dmax, grid, dim3(256), 0, s, d, dmax);
   return hipGetLastError();
 }
 
@@ -3508,16 +3681,26 @@ hipError_t launch_grid(const Dev &d, int32_t *cnt, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_cand(const Dev &d, int32_t *cand_tmp, int r0, int rows, hipStream_t s) {
-  hipLaunchKernelGGL(k_cand, dim3((rows + 3) / 4), dim3(256), 0, s, d, cand_tmp, r0, rows);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !d.xnn) return e;
-  hipLaunchKernelGGL(k_xnn, dim3((rows + 3) / 4), dim3(256), 0, s, d, r0, rows);
+hipError_t launch_near(const Dev &d, int32_t *cand_tmp, const uint32_t *dmax, int r0, int rows,
+                       hipStream_t s) {
+  hipLaunchKernelGGL(k_near, dim3(rows), dim3(256), 0, s, d, cand_tmp, dmax, r0);
   return hipGetLastError();
 }
 
-hipError_t launch_nn_tour(const Dev &d, int64_t *lnn_out, hipStream_t s) {
-  hipLaunchKernelGGL(k_nn_tour, dim3(1), dim3(1024), 0, s, d, lnn_out);
+hipError_t launch_nn_tour(const Dev &d, const int32_t *cand_tmp, uint16_t *near, int64_t *lnn_out,
+                          hipStream_t s) {
+  // neighbours per city in LDS: 16 serve almost every choice; fewer where n is
+  // large (three still serve over half of the choices at n = 20000, one at
+  // the largest n = 65535)
+  constexpr int kLdsBytes = 144 * 1024;
+  const int have = std::min(kNnList, d.xnn ? (int)d.xl : (int)d.cl);
+  const int C = std::max(1, std::min(have, kLdsBytes / (2 * d.n)));
+  const size_t lds = (size_t)d.n * C * sizeof(uint16_t);
+  if (C < have)
+    hipLaunchKernelGGL(k_nn_tour<true>, dim3(1), dim3(1024), lds, s, d, cand_tmp, C, near, lnn_out);
+  else
+    hipLaunchKernelGGL(k_nn_tour<false>, dim3(1), dim3(1024), lds, s, d, cand_tmp, C, near,
+                       lnn_out);
   return hipGetLastError();
 }
 
@@ -3527,28 +3710,13 @@ hipError_t launch_crec(const Dev &d, const int32_t *cand_tmp, float tau0, hipStr
   return hipGetLastError();
 }
 
-hipError_t launch_init_pheromone(const Dev &d, float tau0, hipStream_t s) {
-  if (d.fpre) {
-    hipLaunchKernelGGL(k_fpre, dim3((d.n + 3) / 4), dim3(256), 0, s, d);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (d.rpos) {
-    hipLaunchKernelGGL(k_rpos, dim3((d.n * d.cl + 255) / 256), dim3(256), 0, s, d);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (d.etad) {
-    const size_t total = (size_t)d.n * d.ldn;
-    hipLaunchKernelGGL(k_etad, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, d);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
+hipError_t launch_fill(const Dev &d, float tau0, uint32_t dmax, bool eta_falls, hipStream_t s) {
   size_t total = d.tau ? (size_t)d.n * d.ldn : (size_t)d.n;
-  if (d.spm && total < (size_t)d.n * d.spm_s) total = (size_t)d.n * d.spm_s;
-  if (total < 8) total = 8;
-  if (total < (size_t)d.nbflags) total = (size_t)d.nbflags;
-  hipLaunchKernelGGL(k_init, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, d, tau0);
+  if (d.fpre) total = std::max(total, (size_t)d.n * kFpre);
+  if (d.spm) total = std::max(total, (size_t)d.n * d.spm_s);
+  total = std::max(std::max(total, (size_t)8), (size_t)d.nbflags);
+  hipLaunchKernelGGL(k_fill, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, d, tau0, dmax,
+                     eta_falls ? 1 : 0);
   return hipGetLastError();
 }
 
