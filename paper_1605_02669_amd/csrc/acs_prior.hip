@@ -16,6 +16,8 @@
 // W3[64] | b3[1] (row-major, x @ W + b).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "acs_internal.hpp"
 
 namespace acs {
@@ -205,9 +207,17 @@ __global__ __launch_bounds__(64 * kFwdWaves) void k_prior_forward(const float *P
 // lane l holds rows 4(l/16) + v of one hidden unit, which is the K = 16
 // operand layout.  The weight tiles sit in LDS, one 16-byte entry per lane,
 // and are read where they are used, so that a wave holds at most 256
-// registers and two waves share a SIMD.  The lanes' and waves' partial sums
-// meet in LDS at the end, and each block adds its total to G once per
-// parameter.
+// registers and two waves share a SIMD.
+//
+// A training batch of 65536 rows is one tile per wave, so what a block does
+// once has to be short: the parameters are read into LDS coalesced and each
+// wave builds its share of the tiles from there; at the end the sums over a
+// row's 16 lanes are taken by DPP, every wave stores its partial sums to its
+// own part of LDS (in the lanes' order: no bank conflicts, no atomics), and
+// each thread adds the waves' values of its parameters and adds the total to G.
+// With every wave loading all tiles from global memory and the partial sums
+// meeting by LDS atomics (sixteen lanes on one word), a block's fixed part
+// took 80 us: 65536 rows 90.9 us, now 19.8; 4.2 M rows 303 us, now 245.
 constexpr int kGradWaves = 8;  // two per SIMD: a wave holds 256 registers
 
 // B operand that picks hidden units 16 (2b + odd) + l % 16 out of K block b
@@ -263,57 +273,87 @@ struct LdsNet {
   }
 };
 
+// Operand tile i (see above) for this lane, from the parameters.
+__device__ __forceinline__ u32x4 grad_tile(int i, const float *P, int lane) {
+  const int g = lane >> 4, c16 = lane & 15;
+  bf16x8 w;
+  f32x4 f;
+  if (i < kTW2) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int k = 8 * g + q;
+      w[q] = (__bf16)(k < 4 ? P[OW1 + (k & 3) * H + 16 * i + c16] : 0.f);
+    }
+  } else if (i < kTW3) {
+    const int t = (i - kTW2) >> 1, b = (i - kTW2) & 1;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) w[q] = (__bf16)P[OW2 + perm_k(b, g, q) * H + 16 * t + c16];
+  } else if (i < kTB1) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) w[q] = (__bf16)P[OW3 + perm_k(i - kTW3, g, q)];
+  } else if (i <= kTB3) {
+    const int o = i < kTB2 ? OB1 + 16 * (i - kTB1) : OB2 + 16 * (i - kTB2);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) f[v] = P[i == kTB3 ? OB3 : o + 4 * g + v];
+    return __builtin_bit_cast(u32x4, f);
+  } else if (i < kTPick) {
+    // B of dH1 = dH2 W2^T, tile t, K block b: W2[16t + l%16][perm_k(b, g, q)]
+    const int t = (i - kTW2b) >> 1, b = (i - kTW2b) & 1;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) w[q] = (__bf16)P[OW2 + (16 * t + c16) * H + perm_k(b, g, q)];
+  } else if (i < kTPickX) {
+    w = pick_tile(lane, i - kTPick);
+  } else if (i < kTW3f) {
+    // B operand that picks input column l % 16 (identity)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) w[q] = (__bf16)(8 * g + q == c16 ? 1.f : 0.f);
+  } else {
+    // W3 (bf16) at hidden 16t + 4g + v
+#pragma unroll
+    for (int v = 0; v < 4; ++v) f[v] = (float)(__bf16)P[OW3 + 16 * (i - kTW3f) + 4 * g + v];
+    return __builtin_bit_cast(u32x4, f);
+  }
+  return __builtin_bit_cast(u32x4, w);
+}
+
+// Sum over the 16 lanes of a DPP row, in every lane of the row.
+__device__ __forceinline__ float row_sum(float x) {
+  auto step = [](float v, auto ctrl) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value,
+                                                          0xF, 0xF, false));
+  };
+  x = step(x, std::integral_constant<int, 0xB1>{});   // quad: swap pairs
+  x = step(x, std::integral_constant<int, 0x4E>{});   // quad: swap halves
+  x = step(x, std::integral_constant<int, 0x141>{});  // half row mirrored
+  x = step(x, std::integral_constant<int, 0x140>{});  // row mirrored
+  return x;
+}
+
+// Place of parameter e in a wave's partial sums: dW2 in the order its lanes
+// hold it (entry v of tile (mt, nt) on lane l at ((4mt + nt) 4 + v) 64 + l),
+// the others as in the parameter vector.
+__device__ __forceinline__ int grad_place(int e) {
+  const int w = e - OW2;
+  if (w < 0 || w >= H * H) return e;
+  const int h = w >> 6, c = w & 63;
+  return OW2 + (((4 * (h >> 4) + (c >> 4)) * 4 + (h & 3)) << 6) + 16 * ((h >> 2) & 3) + (c & 15);
+}
+
 __global__ __launch_bounds__(64 * kGradWaves) void k_prior_grad(const float *P, const float *X,
                                                                 const float *Y, int rows,
                                                                 float *G, float *L) {
   __shared__ union alignas(16) {
-    u32x4 tl[kTiles][64];         // operand tiles
-    float red[kPriorParams + 1];  // block totals (the last entry: loss)
+    struct {
+      u32x4 tl[kTiles][64];   // operand tiles
+      float par[kPriorParams];
+    };
+    float red[kGradWaves][kPriorParams + 1];  // waves' sums (the last entry: loss)
   } U;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int g = lane >> 4, c16 = lane & 15;
-  {
-    RegNet N;
-    load_regnet(N, P, lane);
-    // B of dH1 = dH2 W2^T, tile t, K block b: W2[16t + l%16][perm_k(b, g, q)]
-    bf16x8 w2b[4][2];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-          w2b[t][b][q] = (__bf16)P[OW2 + (16 * t + c16) * H + perm_k(b, g, q)];
-    f32x4 w3f[4];  // W3 (bf16) at hidden 16t + 4g + v
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) w3f[t][v] = (float)(__bf16)P[OW3 + 16 * t + 4 * g + v];
-    bf16x8 pickx;  // B operand that picks input column l % 16 (identity)
-#pragma unroll
-    for (int q = 0; q < 8; ++q) pickx[q] = (__bf16)(8 * g + q == c16 ? 1.f : 0.f);
-    // the waves store the tiles in turn
-    auto put = [&](int i, auto v) {
-      if (i % kGradWaves == wv) U.tl[i][lane] = __builtin_bit_cast(u32x4, v);
-    };
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      put(kTW1 + t, N.w1[t]);
-      put(kTW2 + 2 * t, N.w2[t][0]);
-      put(kTW2 + 2 * t + 1, N.w2[t][1]);
-      put(kTB1 + t, N.b1[t]);
-      put(kTB2 + t, N.b2[t]);
-      put(kTW2b + 2 * t, w2b[t][0]);
-      put(kTW2b + 2 * t + 1, w2b[t][1]);
-      put(kTW3f + t, w3f[t]);
-    }
-    put(kTW3, N.w3[0]);
-    put(kTW3 + 1, N.w3[1]);
-    put(kTB3, N.b3);
-    put(kTPick, pick_tile(lane, 0));
-    put(kTPick + 1, pick_tile(lane, 1));
-    put(kTPickX, pickx);
-  }
+  for (int e = threadIdx.x; e < kPriorParams; e += 64 * kGradWaves) U.par[e] = P[e];
+  __syncthreads();
+  for (int i = wv; i < kTiles; i += kGradWaves) U.tl[i][lane] = grad_tile(i, U.par, lane);
   __syncthreads();
   const LdsNet R{U.tl, lane};
   const float inv_rows = 1.f / (float)rows;
@@ -430,8 +470,7 @@ __global__ __launch_bounds__(64 * kGradWaves) void k_prior_grad(const float *P, 
     }
   }
   __syncthreads();  // every wave is done with the tiles
-  for (int e = threadIdx.x; e <= kPriorParams; e += blockDim.x) U.red[e] = 0.f;
-  __syncthreads();
+  float *red = U.red[wv];
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
@@ -439,19 +478,22 @@ __global__ __launch_bounds__(64 * kGradWaves) void k_prior_grad(const float *P, 
       const int h = 16 * mt + 4 * g + v;
 #pragma unroll
       for (int nt = 0; nt < 4; ++nt)
-        atomicAdd(&U.red[OW2 + h * H + 16 * nt + c16], gw2[mt][nt][v]);
-      if (c16 < 4) atomicAdd(&U.red[OW1 + c16 * H + h], gw1[mt][v]);
-      if (c16 == 4) atomicAdd(&U.red[OB1 + h], gw1[mt][v]);
-      atomicAdd(&U.red[OW3 + h], gw3[mt][v]);
-      atomicAdd(&U.red[OB2 + h], gb2[mt][v]);
+        red[OW2 + (((4 * mt + nt) * 4 + v) << 6) + lane] = gw2[mt][nt][v];
+      if (c16 <= 4) red[c16 < 4 ? OW1 + c16 * H + h : OB1 + h] = gw1[mt][v];
+      const float s3 = row_sum(gw3[mt][v]), s2 = row_sum(gb2[mt][v]);
+      if (c16 < 2) red[(c16 ? OB2 : OW3) + h] = c16 ? s2 : s3;
     }
-  if (lane < 16) {
-    atomicAdd(&U.red[OB3], gb3);
-    atomicAdd(&U.red[kPriorParams], loss);
-  }
+  gb3 = row_sum(gb3);
+  loss = row_sum(loss);
+  if (lane < 2) red[lane ? kPriorParams : OB3] = lane ? loss : gb3;
   __syncthreads();
-  for (int e = threadIdx.x; e < kPriorParams; e += blockDim.x) atomicAdd(&G[e], U.red[e]);
-  if (threadIdx.x == 0) atomicAdd(L, U.red[kPriorParams]);
+  for (int e = threadIdx.x; e <= kPriorParams; e += 64 * kGradWaves) {
+    const int at = grad_place(e);
+    float s = U.red[0][at];
+#pragma unroll
+    for (int w = 1; w < kGradWaves; ++w) s += U.red[w][at];
+    atomicAdd(e < kPriorParams ? &G[e] : L, s);
+  }
 }
 
 // Adam (Kingma and Ba, 2015) on the fp32 parameters; clears the gradient.
