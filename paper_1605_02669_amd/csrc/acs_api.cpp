@@ -53,11 +53,14 @@ struct Layout {
 
 constexpr int kEtaEntries = acs::kEtaHostEntries;  // eta^beta for every 16-bit distance
 
-// Cells per side of the selective memory's search grid (about two cities
-// per cell); the grid has at most (side + 1)^2 cells.
+// Cells per side of the selective memory's search grid; the grid has at most
+// (side + 1)^2 cells.  About 64 cities per cell, what a wave reads at once,
+// and at most 961 cells: sixteen ants' bitmaps and 16-bit counts per cell then
+// fit a block's LDS up to the largest n (16 * (8192 + 1924) bytes of 160 KB).
 int grid_side(int n) {
-  return std::min(256, std::max(1, (int)std::ceil(std::sqrt((double)n / 2.0))));
+  return std::min(30, std::max(1, (int)std::ceil(std::sqrt((double)n / 64.0))));
 }
+int grid_cells(int n) { return (grid_side(n) + 1) * (grid_side(n) + 1); }
 
 // The dense fallback first scans the kFpre cities after the candidates; it
 // needs the city after them too.
@@ -84,13 +87,14 @@ Layout make_layout(int n, int m, int cl, int ldn, int memory, int s, int mode) {
                                                                      (sizeof(uint16_t) * ldn)));
   }
   L.crec = take(sizeof(uint4) * (size_t)n * cl);
-  L.cand = take(sizeof(int32_t) * (size_t)n * cl);
+  if (memory == ACS_SPM) L.cand = take(sizeof(int32_t) * (size_t)n * cl);
   L.eta = take(sizeof(float) * kEtaEntries);
   if (memory == ACS_DENSE) {
     L.tau = take(sizeof(float) * (size_t)n * ldn);
     L.etad = take(sizeof(float) * (size_t)n * ldn);
     L.rpos = take(sizeof(int8_t) * (size_t)n * cl);
     L.ctau = take(sizeof(float) * (size_t)n * cl);
+    L.cand = L.ctau;  // while the handle is built; the records keep the lists
     if (mode == ACS_SEQUENTIAL) L.gvis = take(sizeof(uint32_t) * (size_t)m * ((n + 31) / 32));
     if (mode == ACS_SYNC) L.tau2 = take(sizeof(float) * (size_t)n * ldn);
     if (fallback_prefix(n, cl)) {
@@ -103,7 +107,7 @@ Layout make_layout(int n, int m, int cl, int ldn, int memory, int s, int mode) {
     L.spm = take(sizeof(uint32_t) * 2 * (size_t)n * s);
     L.spm_tail = take(sizeof(uint32_t) * (size_t)n);
     L.xnn = take(sizeof(uint32_t) * (size_t)n * std::min(acs::kXnn, n - 1));
-    const size_t cells = (size_t)(grid_side(n) + 1) * (grid_side(n) + 1);
+    const size_t cells = (size_t)grid_cells(n);
     L.gstart = take(sizeof(int32_t) * (cells + 1));
     L.gcnt = take(sizeof(int32_t) * cells);
     L.gcity = take(sizeof(uint32_t) * (size_t)n);
@@ -113,7 +117,7 @@ Layout make_layout(int n, int m, int cl, int ldn, int memory, int s, int mode) {
     L.upd_next = take(sizeof(int32_t) * 2 * (size_t)m);
     L.upd_head = take(sizeof(int32_t) * (size_t)n);
   }
-  if (mode == ACS_SYNC) L.bflags = take(sizeof(uint64_t) * 16 * (size_t)((m + 15) / 16 + 1));
+  if (mode == ACS_SYNC) L.bflags = take(sizeof(uint32_t) * acs::sync_barrier_words(m));
   if (memory == ACS_DENSE) {
     L.tours = take(tour_bytes);
   } else {
@@ -420,6 +424,7 @@ int init_handle(acs_t *h, const double *coords_xy, int32_t n, const acs_params *
   d.cl = h->cl;
   d.ldn = h->ldn;
   d.spm_s = (int)p->spm_s;
+  d.vw = (n + 31) / 32 + (p->memory == ACS_SPM ? (grid_cells(n) + 1) / 2 : 0);
   d.xy = reinterpret_cast<const double *>(w + h->L.xy);
   d.dist = reinterpret_cast<const uint16_t *>(w + h->L.dist);
   d.crec = reinterpret_cast<const uint4 *>(w + h->L.crec);
@@ -458,8 +463,8 @@ int init_handle(acs_t *h, const double *coords_xy, int32_t n, const acs_params *
   d.sync = reinterpret_cast<uint32_t *>(w + h->L.sync);
   d.wait_limit = p->wait_limit;
   if (p->mode == ACS_SYNC) {
-    d.bflags = reinterpret_cast<unsigned long long *>(w + h->L.bflags);
-    d.nbflags = 16 * ((m + 15) / 16 + 1);
+    d.bflags = reinterpret_cast<uint32_t *>(w + h->L.bflags);
+    d.nbflags = (int32_t)acs::sync_barrier_words(m);
   }
 
   if (p->mode == ACS_SYNC) {
@@ -677,7 +682,14 @@ int acs_candidates(acs_t *h, int32_t *out, size_t count) {
   const size_t need = (size_t)h->n * h->cl;
   if (!out || count < need) return fail(ACS_E_BUFSIZE, "need %zu ints", need);
   HIP_TRY(hipStreamSynchronize(h->stream));
-  HIP_TRY(hipMemcpy(out, h->ws + h->L.cand, need * sizeof(int32_t), hipMemcpyDeviceToHost));
+  if (h->p.memory == ACS_SPM) {
+    HIP_TRY(hipMemcpy(out, h->ws + h->L.cand, need * sizeof(int32_t), hipMemcpyDeviceToHost));
+    return ACS_OK;
+  }
+  std::vector<uint32_t> rec(4 * need);  // dense memory: first word of each record
+  HIP_TRY(hipMemcpy(rec.data(), h->ws + h->L.crec, rec.size() * sizeof(uint32_t),
+                    hipMemcpyDeviceToHost));
+  for (size_t e = 0; e < need; ++e) out[e] = (int32_t)rec[4 * e];
   return ACS_OK;
 }
 

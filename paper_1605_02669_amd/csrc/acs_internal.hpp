@@ -12,7 +12,8 @@ namespace acs {
 // Record of candidate k of city i (the cl nearest neighbours of Sec. 3,
 // sorted by (d, j)), one 16-byte load per lane:
 //   x = neighbour j, y = d(i, j), z = bits of eta^beta(d),
-//   w = bits of the pheromone tau(i, j) (the home of that directed entry).
+//   w = bits of the pheromone tau(i, j) (the home of that directed entry), or
+//       with the selective memory the grid cell of j.
 
 // Device view of one colony.  Row-major matrices use the padded stride ldn.
 struct Dev {
@@ -60,6 +61,9 @@ struct Dev {
   const uint32_t *gcity;   //   n
   const double2 *gxy;      //   n
   int32_t gnx, gny;
+  int32_t vw;              // LDS words of one ant: the visited bitmap and, with
+                           //   the selective memory, the unvisited cities of
+                           //   every grid cell as 16-bit counts
   double gx0, gy0, gh, ginv;
   int32_t *upd_rec;        // SPM synchronous updates of one step: record
   int32_t *upd_nb;         //   ... and neighbour of update e = 2 * ant + w,
@@ -73,8 +77,7 @@ struct Dev {
                                  // unvisited cities at fallback steps,
                                  // compare-and-swap retries, local-search moves
   uint32_t *sync;          // [0] unused, [1] error flag
-  unsigned long long *bflags;  // synchronous mode: grid barrier flags, one per
-                               //   block, 16 words (128 bytes) apart, from word 16
+  uint32_t *bflags;            // synchronous mode: the grid barrier's words
   int32_t nbflags;             //   words in bflags
   uint32_t wait_limit;         // polls before a bounded wait gives up (0: the
                                //   kernels' own limits)
@@ -125,6 +128,24 @@ hipError_t launch_fill(const Dev &d, float tau0, uint32_t dmax, bool eta_falls, 
 hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, int lanes,
                             int queued, hipStream_t s, hipEvent_t ev0 = nullptr,
                             hipEvent_t ev1 = nullptr);
+// Ants per block of the synchronous kernels.  Every phase of a step lasts as
+// long as its slowest ant, and the waves of a SIMD run it in lockstep, so the
+// ants are spread over all compute units (256), at most kSyncMaxAnts per
+// block.
+constexpr int kSyncMaxAnts = 16, kSyncBlocks = 256;
+inline int sync_ants_per_block(int m) {
+  const int a = (m + kSyncBlocks - 1) / kSyncBlocks;
+  return a < kSyncMaxAnts ? a : kSyncMaxAnts;
+}
+inline int sync_blocks(int m) {
+  return (m + sync_ants_per_block(m) - 1) / sync_ants_per_block(m);
+}
+// Words of the grid barrier: the XCDs' lists and mailboxes, a word per block.
+constexpr int kXcds = 8;
+inline size_t sync_barrier_words(int m) {
+  const size_t g = (size_t)sync_blocks(m);
+  return kXcds * (((g + 31) & ~(size_t)31) + 32) + g;
+}
 // Largest m a synchronous launch can keep resident for this instance.
 int max_sync_ants(const Dev &d, int memory);
 hipError_t launch_best_global(const Dev &d, const Iter &it, int memory,
