@@ -140,6 +140,24 @@ inline int sync_ants_per_block(int m) {
 inline int sync_blocks(int m) {
   return (m + sync_ants_per_block(m) - 1) / sync_ants_per_block(m);
 }
+// Dense synchronous construction with the candidate entries' pheromone in
+// every block's LDS (k_construct_sync_lds).  Its ants per block: about 32
+// blocks, up to 64 as long as they hold the ants, at least 4 each; a block then
+// has a thread for every ant of the colony.
+inline int sync_lds_ants_per_block(int m) {
+  const int a = m <= 512 ? (m + 31) / 32 : (m + 63) / 64;
+  return a < 4 ? 4 : a;
+}
+// It is taken where 64 blocks hold the ants, n * cl floats and 16 ants' bitmaps
+// fit a block's LDS, and the blocks' words (two sets of 128 bytes each) fit the
+// place of ctau, which it does not use.
+constexpr size_t kSyncLdsBytes = 156 * 1024;
+inline bool sync_lds(int n, int m, int cl) {
+  const int a = sync_lds_ants_per_block(m);
+  return m <= 64 * kSyncMaxAnts &&
+         (size_t)n * cl * 4 + (size_t)kSyncMaxAnts * ((n + 31) / 32) * 4 <= kSyncLdsBytes &&
+         (size_t)((m + a - 1) / a) * 256 <= (size_t)n * cl * 4;
+}
 // Words of the grid barrier: the XCDs' lists and mailboxes, a word per block.
 constexpr int kXcds = 8;
 inline size_t sync_barrier_words(int m) {

@@ -31,6 +31,11 @@ namespace acs {
 namespace {
 
 constexpr uint32_t kNone = 0xffffffffu;
+// fourth word of a buffer resource for untyped dword loads (gfx9 family)
+constexpr int kBufWord3 = 0x00020000;
+// cache policy of a buffer load that reads what the device's coherence point
+// holds (sc1), for values other waves update during the launch
+constexpr int kCoherent = 16;
 
 // ---------------------------------------------------------------------------
 // Philox4x32-10 (Salmon et al., SC 2011): ten rounds of the 4x32 S-box with
@@ -273,8 +278,8 @@ __device__ __forceinline__ bool reached(const uint32_t *flag, uint32_t epoch) {
          0;
 }
 
-// Polls until `done` holds on every lane of the first wave; false when the
-// wait gave up.  Once any block has given up, no later wait polls long either
+// Polls until `done` holds on every lane of the wave; false when the wait
+// gave up.  Once any block has given up, no later wait polls long either
 // (looked at every 64th poll, so a poll costs the flag loads only).
 template <class F>
 __device__ __forceinline__ bool bounded_wait(const Dev &D, F done) {
@@ -284,7 +289,7 @@ __device__ __forceinline__ bool bounded_wait(const Dev &D, F done) {
         __hip_atomic_load(D.sync + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
       return false;
     if (spins >= (D.wait_limit ? D.wait_limit : (1u << 22))) {
-      if (threadIdx.x == 0)
+      if ((threadIdx.x & 63) == 0)
         __hip_atomic_store(D.sync + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return false;
     }
@@ -998,24 +1003,45 @@ __device__ __forceinline__ int pick_candidate(const Iter &A, int lane, int cl, C
   return uni(k);
 }
 
+// The prefix of a city's fallback (D.fpre): two cities per lane, and the bound
+// on every weight beyond them.
+struct PrefixRow {
+  uint4 e;
+  float bound;
+};
+// Without a prefix (D.fpre null) the loads go to the first record and, by the
+// buffer's bounds check, to a zero: no branch, so that a caller's loads in
+// flight need no wait where paths meet.  (The bound is a vector load because
+// LDS reads would have to wait for a scalar one in flight.)
+__device__ __forceinline__ PrefixRow prefix_row(const Dev &D, int cur, int lane) {
+  const uint4 *row = D.fpre ? D.fpre + (size_t)cur * (kFpre / 2) + lane : D.crec;
+  const __amdgpu_buffer_rsrc_t brs =
+      __builtin_amdgcn_make_buffer_rsrc(D.fbound, 0, D.fbound ? D.n * 4 : 0, kBufWord3);
+  return PrefixRow{*row, __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(brs, cur * 4, 0, 0))};
+}
+
 // Alg. 2, empty candidate set: greedy over every unvisited city, ties ->
-// lowest index.  With a prefix (D.fpre), the kFpre cities after the
-// candidates come first, two per lane; when the best unvisited one beats
+// lowest index.  With a prefix (D.fpre; pre: cur's), the kFpre cities after
+// the candidates come first, two per lane; when the best unvisited one beats
 // D.fbound[cur] strictly, no city beyond the prefix can reach or tie it (the
 // candidates are all visited), so it is the answer of the whole scan.
-// Otherwise each lane scans eight consecutive cities per round.  The loads
-// of round r + 1 are issued before round r is examined (every round loads,
-// at an address clamped into the padded row, so the number of loads in
-// flight is fixed and the wait covers round r only).
+// Otherwise each lane scans eight consecutive cities per round, the loads of
+// several rounds issued before the first is examined (at addresses clamped
+// into the padded row, so that their number is fixed).  In the asynchronous
+// kernels one round is ahead (registers set their occupancy); in the
+// synchronous one (COHERENT) every step waits for the slowest ant, whose scan
+// this is: three rounds at a time, by 16-byte coherent loads (eight 4-byte
+// ones and one round ahead made the scan 28 k cycles at n = 2392).
 template <bool COHERENT>
 __device__ __forceinline__ Pick fallback_dense(const Dev &D, const uint32_t *vis, int cur,
-                                               int lane, const float *tsrc = nullptr) {
+                                               int lane, const PrefixRow &pre,
+                                               const float *tsrc = nullptr) {
   const int n = D.n;
   Pick p;
   const float *trow = (tsrc ? tsrc : D.tau) + (size_t)cur * D.ldn;
   if (D.fpre) {
-    const uint4 pe = D.fpre[(size_t)cur * (kFpre / 2) + lane];
-    const float fb = D.fbound[cur];
+    const uint4 pe = pre.e;
+    const float fb = pre.bound;
     const uint32_t j0 = pe.x & 0xffffu, j1 = pe.z & 0xffffu;
     const float t0 = COHERENT ? tau_load(trow + j0) : trow[j0];
     const float t1 = COHERENT ? tau_load(trow + j1) : trow[j1];
@@ -1050,11 +1076,18 @@ __device__ __forceinline__ Pick fallback_dense(const Dev &D, const uint32_t *vis
     float t[8], e[8];
     uint4 d;
   };
+  const __amdgpu_buffer_rsrc_t trs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float *>(trow), 0, D.ldn * (int)sizeof(float), kBufWord3);
   auto fetch = [&](int r, Round &x) {
     const int j = min(8 * lane + 512 * r, D.ldn - 8);
     if (COHERENT) {
+      const auto a = __builtin_amdgcn_raw_buffer_load_b128(trs, 4 * j, 0, kCoherent);
+      const auto b = __builtin_amdgcn_raw_buffer_load_b128(trs, 4 * j, 16, kCoherent);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) x.t[q] = tau_load(trow + j + q);
+      for (int q = 0; q < 4; ++q) {
+        x.t[q] = __uint_as_float(a[q]);
+        x.t[4 + q] = __uint_as_float(b[q]);
+      }
     } else {
       const float4 a = *reinterpret_cast<const float4 *>(trow + j);
       const float4 b = *reinterpret_cast<const float4 *>(trow + j + 4);
@@ -1067,24 +1100,39 @@ __device__ __forceinline__ Pick fallback_dense(const Dev &D, const uint32_t *vis
     x.e[4] = b.x; x.e[5] = b.y; x.e[6] = b.z; x.e[7] = b.w;
     x.d = *reinterpret_cast<const uint4 *>(drow + j);
   };
-  Round cr;
-  fetch(0, cr);
-  for (int r = 0; r < rounds; ++r) {
-    Round nr;
-    fetch(min(r + 1, rounds - 1), nr);
+  auto examine = [&](int r, const Round &x) {
     const int j0 = 8 * lane + 512 * r;
     uint32_t bits = (vis[min(j0, n - 1) >> 5] >> (j0 & 31)) & 0xffu;
     if (j0 >= n) bits = 0xffu;
     else if (j0 + 8 > n) bits |= (0xffu << (n - j0)) & 0xffu;
-    const uint32_t dw[4] = {cr.d.x, cr.d.y, cr.d.z, cr.d.w};
+    const uint32_t dw[4] = {x.d.x, x.d.y, x.d.z, x.d.w};
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      const float v = cr.t[q] * cr.e[q];
+      const float v = x.t[q] * x.e[q];
       if (!((bits >> q) & 1u) && (bj == kNone || v > bv)) {
-        bv = v; bj = (uint32_t)(j0 + q); bt = cr.t[q]; bd = (dw[q >> 1] >> (16 * (q & 1))) & 0xffffu;
+        bv = v; bj = (uint32_t)(j0 + q); bt = x.t[q]; bd = (dw[q >> 1] >> (16 * (q & 1))) & 0xffffu;
       }
     }
-    cr = nr;
+  };
+  if (COHERENT) {
+    for (int r = 0; r < rounds; r += 3) {
+      Round x[3];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) fetch(min(r + i, rounds - 1), x[i]);
+      examine(r, x[0]);
+#pragma unroll
+      for (int i = 1; i < 3; ++i)
+        if (r + i < rounds) examine(r + i, x[i]);
+    }
+  } else {
+    Round cr;
+    fetch(0, cr);
+    for (int r = 0; r < rounds; ++r) {
+      Round nr;
+      fetch(min(r + 1, rounds - 1), nr);
+      examine(r, cr);
+      cr = nr;
+    }
   }
   const uint32_t mx = wave_umax_u(bj == kNone ? 0u : __float_as_uint(bv));
   const uint32_t jn = wave_umin_u((bj != kNone && __float_as_uint(bv) == mx) ? bj : kNone);
@@ -1098,14 +1146,12 @@ __device__ __forceinline__ Pick fallback_dense(const Dev &D, const uint32_t *vis
   return p;
 }
 
-// tsrc: the dense pheromone matrix to read (default D.tau)
-template <bool COHERENT>
+// The choice from the current city's records; a fallback loads its prefix.
 __device__ __forceinline__ Pick select_dense(const Dev &D, const Iter &A, const uint32_t *vis,
-                                             int cur, int lane, uint4 rec, Cand c, uint2 q,
-                                             const float *tsrc = nullptr) {
+                                             int cur, int lane, uint4 rec, Cand c, uint2 q) {
   Pick p;
   const int k = pick_candidate(A, lane, D.cl, c, q, p.kind);
-  if (k < 0) return fallback_dense<COHERENT>(D, vis, cur, lane, tsrc);
+  if (k < 0) return fallback_dense<false>(D, vis, cur, lane, prefix_row(D, cur, lane));
   p.k = k;
   p.next = (int)rdlane(rec.x, k);
   p.d = rdlane(rec.y, k);
@@ -1187,17 +1233,35 @@ __global__ __launch_bounds__(1024) void k_construct_sync_dense(Dev D, Iter A) {
   // the previous step's crossing (double-buffered schedule)
   int pu = -1, pv = -1, pk = -1, pk2 = -1;
   float pval = 0.f;
+  // what does not change while the ants run is loaded before the barrier that
+  // the city's pheromone has to wait for: its records, its positions in its
+  // candidates' lists and its fallback's prefix
+  uint4 rec = D.crec[(size_t)cur * cl + kl];
+  int rpos = D.rpos[(size_t)cur * cl + kl];
+  PrefixRow pre = prefix_row(D, cur, lane);
   for (int t = 1; t < n; ++t) {
     Pick p{};
+    int k2 = -1;
     const int rb = dbuf ? (t & 1) : 0;
     if ((t & 63) == 0) draws = philox_batch(A, ant, t, lane);
     if (active) {
-      uint4 rec = D.crec[(size_t)cur * cl + kl];
       const float *ct = rb == 0 ? cand_tau(D, cur, kl) : D.ctau + (size_t)cur * cl + kl;
       rec.w = __float_as_uint(tau_load(ct));
       const Cand c = weigh(D, vis, lane, rec);
-      p = select_dense<true>(D, A, vis, cur, lane, rec, c, draw_of(draws, t),
-                             rb == 0 ? D.tau : D.tau2);
+      const int k = pick_candidate(A, lane, cl, c, draw_of(draws, t), p.kind);
+      if (k >= 0) {
+        p.k = k;
+        p.next = (int)rdlane(rec.x, k);
+        p.d = rdlane(rec.y, k);
+        p.tval = __uint_as_float(rdlane(rec.w, k));
+        k2 = (int)rdlane((uint32_t)rpos, k);
+      } else {
+        p = fallback_dense<true>(D, vis, cur, lane, pre, rb == 0 ? D.tau : D.tau2);
+        k2 = cand_pos(D, p.next, cur, lane);
+      }
+      rec = D.crec[(size_t)p.next * cl + kl];
+      rpos = D.rpos[(size_t)p.next * cl + kl];
+      pre = prefix_row(D, p.next, lane);
       c_greedy += p.kind == 0;
       c_roul += p.kind == 1;
       if (p.kind == 2) { ++c_fb; c_fbu += (uint64_t)(n - t); }
@@ -1209,7 +1273,6 @@ __global__ __launch_bounds__(1024) void k_construct_sync_dense(Dev D, Iter A) {
       // crossings of steps t - 1 and t into buffer (t + 1) % 2: lanes 0 and
       // 1 the previous crossing's two entries, lanes 2 and 3 this one's
       if (active) {
-        const int k2 = cand_pos(D, p.next, cur, lane);
         const int wb = rb ^ 1;
         float *h = nullptr;
         unsigned int seen = 0;
@@ -1234,7 +1297,6 @@ __global__ __launch_bounds__(1024) void k_construct_sync_dense(Dev D, Iter A) {
     } else if (t % A.lperiod == 0) {
       grid_barrier_f(D, gbar, barrier_epoch(A, ++bar));
       if (active) {
-        const int k2 = cand_pos(D, p.next, cur, lane);
         float *h = lane == 0 ? home(D, cur, p.next, p.k) : home(D, p.next, cur, k2);
         if (lane < 2 && !map_fixed(p.tval, A.a_loc, A.b_loc))
           c_retry += cas_apply(h, __float_as_uint(p.tval), A.a_loc, A.b_loc);
@@ -1264,11 +1326,245 @@ __global__ __launch_bounds__(1024) void k_construct_sync_dense(Dev D, Iter A) {
   }
 }
 
-// Buffer 1 of the double-buffered synchronous schedule from buffer 0 (dir 0),
+// The same construction where the pheromone of all candidate entries fits a
+// block's LDS: every block keeps its own copy and applies every ant's crossings
+// to it, so a step needs neither a coherent read of the row nor a
+// compare-and-swap on memory, whose retries on the edges that several ants
+// cross (1800 cycles each across XCDs) and whose round trips made up most of
+// a step.  What the blocks exchange is one word per ant and update step, the
+// crossing, tagged with the step; a block goes on when it has read all m of
+// them, so the words are the barrier too (two sets in turn: a block can be one
+// update step ahead of another that still reads).  The host takes this kernel
+// for up to 1024 ants in at most 64 blocks, one word per thread: that many
+// blocks poll each other's lines in about 3000 cycles, while 250 need 7000, and
+// a grid barrier before the words made it slower than the kernel above (n =
+// 1500, m = n, cl = 16: 6.5 against 5.3 us per step).  The map is the same for
+// all crossings, so their order inside a step does not matter.
+//
+// Entries of edges that are not in a candidate list (fallbacks, 2% of the
+// steps) stay in memory, double-buffered: buffer b (0: tau, 1: tau2) is read,
+// the crossings of this update step and of the previous one go to the other,
+// before the ant's word is published.  The closing edges are one more
+// exchange; their non-candidate entries go to the buffer last read.
+//
+// m = n, us per step: n = 198 5.6 -> 2.8, n = 1000 4.7 -> 3.1; 64 ants, n =
+// 1000: 4.2 -> 2.4.  About 800 cycles of a step are the choice, the rest the
+// words' way (a store and a load beyond the XCD) and their application.
+//
+// HALF: cl <= 32, the maximum over 32 lanes.
+struct Crossing {
+  int u, v, k, kr;  // edge, position of v in u's list and of u in v's (-1: none)
+};
+__device__ __forceinline__ uint64_t pack_crossing(int t, const Crossing &c) {
+  return (uint64_t)t << 46 | (uint64_t)c.u << 30 | (uint64_t)c.v << 14 | (uint64_t)(c.k + 1) << 7 |
+         (uint64_t)(c.kr + 1);
+}
+__device__ __forceinline__ Crossing unpack_crossing(uint64_t w) {
+  return Crossing{(int)(w >> 30) & 0xffff, (int)(w >> 14) & 0xffff, (int)((w >> 7) & 127) - 1,
+                  (int)(w & 127) - 1};
+}
+
+// A block barrier that orders LDS only: global loads and stores stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <bool HALF>
+__global__ __launch_bounds__(1024) void k_construct_sync_lds(Dev D, Iter A) {
+  extern __shared__ uint32_t smem[];  // n x cl pheromone, then the ants' bitmaps
+  const int lane = threadIdx.x & 63;
+  const int wv = threadIdx.x >> 6;
+  const int ant = uni(blockIdx.x * (blockDim.x >> 6) + wv);
+  const bool active = ant < D.m;
+  const int n = D.n, cl = D.cl, m = D.m;
+  const int W = (n + 31) >> 5;
+  const int kl = lane < cl ? lane : cl - 1;
+  uint32_t *vis = smem + n * cl + wv * W;
+  const float al = A.a_loc, bl = A.b_loc;
+  // a block's words of one set in a 128-byte line of their own
+  const int apb = (int)(blockDim.x >> 6);
+  unsigned long long *words = reinterpret_cast<unsigned long long *>(D.ctau);
+  const size_t set_words = (size_t)kSyncMaxAnts * gridDim.x;
+  // the word this thread reads
+  const bool mine = (int)threadIdx.x < m;
+  const size_t slot = (size_t)kSyncMaxAnts * (threadIdx.x / apb) + threadIdx.x % apb;
+  __shared__ uint64_t s_word[kSyncMaxAnts];
+
+  for (int e = threadIdx.x; e < n * cl; e += blockDim.x) smem[e] = D.crec[e].w;
+  for (int w = lane; w < W; w += 64) vis[w] = 0u;
+  __syncthreads();
+  uint4 draws = philox_batch(A, ant, 0, lane);
+  uint64_t greedy = __ballot((draws.x >> 8) < A.q0_24);  // the 64 steps' greedy draws
+  const int start = (int)__umulhi(rdlane(draws.z, 0), (uint32_t)n);
+  if (lane == 0) vis[start >> 5] |= 1u << (start & 31);
+  int tb = start;
+
+  const uint64_t clmask = cl >= 64 ? ~0ull : (1ull << cl) - 1;
+  int cur = start;
+  int64_t len = 0;
+  uint32_t c_roul = 0, c_fb = 0, c_retry = 0;
+  uint64_t c_fbu = 0;
+  uint32_t upds = 0;                    // update steps so far; buffer upds & 1 is read
+  uint32_t left = A.lperiod;            // steps to the next one
+  Crossing last{-1, -1, 0, 0};          // of the previous update step
+  float lval = 0.f;
+  uint4 rec = D.crec[(size_t)cur * cl + kl];
+  int8_t rpos = D.rpos[(size_t)cur * cl + kl];
+  PrefixRow pre = prefix_row(D, cur, lane);
+  for (int t = 1; t <= n; ++t) {
+    Crossing x{cur, start, -1, -1};
+    float val = 0.f;
+    float *const rd = (upds & 1) ? D.tau2 : D.tau, *const wr = (upds & 1) ? D.tau : D.tau2;
+    const int tl = t & 63;
+    if (tl == 0) {
+      draws = philox_batch(A, ant, t, lane);
+      greedy = __ballot((draws.x >> 8) < A.q0_24);
+    }
+    if (active && t < n) {
+      const uint32_t tau = smem[cur * cl + kl];
+      const bool unv = !((vis[rec.x >> 5] >> (rec.x & 31)) & 1u);
+      const uint64_t umask = __ballot(unv) & clmask;
+      uint32_t d;
+      if (umask) {
+        const float w = unv ? __uint_as_float(tau) * __uint_as_float(rec.z) : 0.f;
+        if ((greedy >> tl) & 1u) {
+          // Eq. 1: maximum weight, lowest position
+          const uint32_t wb = __float_as_uint(w);
+          const uint32_t mx = rows_umax_s<HALF ? 32 : 64>(wb);
+          x.k = (int)__builtin_ctzll(__ballot(wb == mx) & umask);
+        } else {
+          // Eq. 2 by roulette, as in pick_candidate
+          float P = w;
+          for (int off = 1; off < cl; off <<= 1) {
+            const float o = __shfl_up(P, off, 64);
+            if (lane >= off) P = P + o;
+          }
+          const float total = __uint_as_float(rdlane(__float_as_uint(P), cl - 1));
+          const float r = ((float)(rdlane(draws.y, tl) >> 8) * 0x1p-24f) * total;
+          const uint64_t sel = __ballot(P > r) & umask;
+          x.k = sel ? (int)__builtin_ctzll(sel) : 63 - (int)__builtin_clzll(umask);
+          ++c_roul;
+        }
+        x.v = (int)rdlane(rec.x, x.k);
+        x.kr = (int)rdlane((uint32_t)(int)rpos, x.k);
+        d = rdlane(rec.y, x.k);
+        val = __uint_as_float(rdlane(tau, x.k));
+      } else {
+        const Pick p = fallback_dense<true>(D, vis, cur, lane, pre, rd);
+        x.v = p.next;
+        x.kr = cand_pos(D, p.next, cur, lane);
+        d = p.d;
+        val = p.tval;
+        ++c_fb;
+        c_fbu += (uint64_t)(n - t);
+      }
+      if (lane == 0) mark(vis, x.v);
+      len += d;
+    } else if (active) {
+      x.k = cand_pos(D, cur, start, lane);
+      x.kr = cand_pos(D, start, cur, lane);
+      len += D.dist[(size_t)cur * D.ldn + start];
+    }
+    const bool upd = t == n || --left == 0;
+    if (left == 0) left = A.lperiod;
+    // vmcnt(0): this step's rows have long arrived; without it the loads below
+    // would wait, through the registers they reuse, for the store of the word
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    if (active && upd) {
+      // non-candidate entries of the previous update step's crossing (lanes 0
+      // and 1) and of this one (2 and 3; the closing edge's follow below); a
+      // compare-and-swap whose result has come back is performed
+      const Crossing &c = lane < 2 ? last : x;
+      const bool fwd = (lane & 1) == 0;
+      const float seen = lane < 2 ? lval : val;
+      if (lane < (t < n ? 4 : 0) && c.u >= 0 && (fwd ? c.k : c.kr) < 0 &&
+          !map_fixed(seen, al, bl))
+        c_retry += cas_apply(wr + (size_t)(fwd ? c.u : c.v) * D.ldn + (fwd ? c.v : c.u),
+                             __float_as_uint(seen), al, bl);
+      last = x;
+      lval = val;
+      if (lane == 0) s_word[wv] = pack_crossing(t, x);
+    }
+    unsigned long long *const set = words + (upds & 1) * set_words;
+    if (upd) {
+      // every wave has read the block's copy for this step and left its word,
+      // which go out in one store
+      lds_barrier();
+      if ((int)threadIdx.x < apb && (int)(blockIdx.x * apb + threadIdx.x) < m)
+        __hip_atomic_store(set + (size_t)kSyncMaxAnts * blockIdx.x + threadIdx.x,
+                           (unsigned long long)s_word[threadIdx.x], __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // the next city's rows while the words travel (every ant, every step: no
+    // branch, and the byte is widened where it is used, so nothing waits here)
+    rec = D.crec[(size_t)x.v * cl + kl];
+    rpos = D.rpos[(size_t)x.v * cl + kl];
+    pre = prefix_row(D, x.v, lane);
+    if (active && t < n) {
+      tb = (int)wrlane((uint32_t)x.v, tl, (uint32_t)tb);
+      if ((tl == 63 || t == n - 1) && lane <= tl) D.tours[(size_t)ant * n + (t & ~63) + lane] = tb;
+    }
+    if (upd) {
+      uint64_t w = 0;
+      if (wv * 64 < m)
+        bounded_wait(D, [&]() {
+          if (mine) w = __hip_atomic_load(set + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          return !mine || (int)(w >> 46) == t;
+        });
+      if (mine && (int)(w >> 46) == t) {
+        // the map on this block's copy of the crossing's candidate entries,
+        // both side by side
+        const Crossing c = unpack_crossing(w);
+        int e0 = c.k >= 0 ? c.u * cl + c.k : -1, e1 = c.kr >= 0 ? c.v * cl + c.kr : -1;
+        uint32_t x0 = smem[max(e0, 0)], x1 = smem[max(e1, 0)];
+        while (e0 >= 0 || e1 >= 0) {
+          const uint32_t y0 = __float_as_uint(fmaf(al, __uint_as_float(x0), bl));
+          const uint32_t y1 = __float_as_uint(fmaf(al, __uint_as_float(x1), bl));
+          uint32_t g0 = x0, g1 = x1;
+          if (e0 >= 0 && y0 != x0) g0 = atomicCAS(&smem[e0], x0, y0);
+          if (e1 >= 0 && y1 != x1) g1 = atomicCAS(&smem[e1], x1, y1);
+          if (g0 == x0) e0 = -1;
+          if (g1 == x1) e1 = -1;
+          x0 = g0;
+          x1 = g1;
+        }
+      }
+      lds_barrier();
+      ++upds;
+    }
+    if (t < n) cur = x.v;
+  }
+  // every block's copy is the final one: each writes its share back
+  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n * cl; e += gridDim.x * blockDim.x)
+    const_cast<uint4 *>(D.crec)[e].w = smem[e];
+  if (active) {
+    // the closing edge's non-candidate entries, into the buffer last read
+    float *const fin = ((upds - 1) & 1) ? D.tau2 : D.tau;
+    if (lane < 2 && (lane == 0 ? last.k : last.kr) < 0) {
+      float *h = fin + (size_t)(lane == 0 ? last.u : last.v) * D.ldn +
+                 (lane == 0 ? last.v : last.u);
+      c_retry += cas_apply(h, __float_as_uint(tau_load(h)), al, bl);
+    }
+    c_retry = (uint32_t)uni((int)(rdlane(c_retry, 0) + rdlane(c_retry, 1) + rdlane(c_retry, 2) +
+                                  rdlane(c_retry, 3)));
+    if (lane == 0) {
+      D.lens[ant] = len;
+      add_counters(D, (uint32_t)(n - 1) - c_roul - c_fb, c_roul, c_fb, c_fbu, c_retry);
+    }
+  }
+}
+
+// Buffer 1 of the double-buffered synchronous schedules from buffer 0 (dir 0),
 // or buffer 0 from buffer 1 (dir 1) when the construction ended in buffer 1.
-__global__ __launch_bounds__(256) void k_sync_buf(Dev D, int dir) {
+// words > 0: the candidate entries are not part of it (k_construct_sync_lds);
+// dir 0 clears that many words of the place of the exchanged crossings.
+__global__ __launch_bounds__(256) void k_sync_buf(Dev D, int dir, int words) {
   const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (e < (size_t)D.n * D.cl) {
+  if (words > 0) {
+    if (dir == 0 && e < (size_t)words) D.ctau[e] = 0.f;
+  } else if (e < (size_t)D.n * D.cl) {
     if (dir == 0)
       D.ctau[e] = __uint_as_float(D.crec[e].w);
     else
@@ -1344,7 +1640,7 @@ __global__ __launch_bounds__(64 * kSeqWaves) void k_construct_seq_dense(Dev D, I
         const uint4 draws = philox_batch(A, a, t & ~63, lane);
         const uint4 rec = D.crec[(size_t)cur * cl + kl];
         const Cand c = weigh(D, vis, lane, rec);
-        p = select_dense<false>(D, A, vis, cur, lane, rec, c, draw_of(draws, t));
+        p = select_dense(D, A, vis, cur, lane, rec, c, draw_of(draws, t));
         // position of cur in the chosen city's list, for the second entry
         if (upd) kr = p.k >= 0 ? (int)D.rpos[(size_t)cur * cl + p.k] : cand_pos(D, p.next, cur, lane);
       }
@@ -1494,7 +1790,7 @@ __device__ __forceinline__ void ant_async_dense(const Dev &D, const Iter &A, int
     }
     if (t == n) break;
     // 3. selection
-    const Pick p = select_dense<false>(D, A, vis, cur, lane, rec, c, draw_of(draws, t));
+    const Pick p = select_dense(D, A, vis, cur, lane, rec, c, draw_of(draws, t));
     c_kind += 1ull << (21 * p.kind);
     if (p.kind == 2) c_fbu += (uint64_t)(n - t);
     if (lane == 0) mark(vis, p.next);
@@ -1578,11 +1874,6 @@ constexpr int kQRing = 256;   // ring entries per ant wave (power of 2, >= 64 + 
 constexpr uint32_t kQSpin = 1u << 22;
 constexpr uint32_t kQIdle = 1u << 20;
 constexpr uint32_t kNoEntry = 0xffffffffu;
-// fourth word of a buffer resource for untyped dword loads (gfx9 family)
-constexpr int kBufWord3 = 0x00020000;
-// cache policy of a buffer load that reads what the device's coherence point
-// holds (sc1), for values other waves update during the launch
-constexpr int kCoherent = 16;
 
 struct QRing {
   uint4 *ent;      // [ant wave][kQRing]
@@ -1852,7 +2143,7 @@ __device__ __forceinline__ void ant_queued(const Dev &D, const Iter &A, int ant,
         int next, k;
         uint32_t d, tv;
         if (__builtin_expect(umask == 0, 0)) {
-          const Pick p = fallback_dense<false>(D, vis, cur, lane);
+          const Pick p = fallback_dense<false>(D, vis, cur, lane, prefix_row(D, cur, lane));
           next = p.next;
           k = -1;
           d = p.d;
@@ -3854,6 +4145,9 @@ static hipError_t queued_ants_per_block(int m, int *na) {
 // The selective memory's common shapes get kernels with s = 8 and the
 // candidate lanes fixed (the trail lookup unrolls).
 static const void *sync_kernel(const Dev &d, int memory) {
+  if (memory == 0 && sync_lds(d.n, d.m, d.cl))
+    return d.cl <= 32 ? reinterpret_cast<const void *>(&k_construct_sync_lds<true>)
+                      : reinterpret_cast<const void *>(&k_construct_sync_lds<false>);
   if (memory == 0) return reinterpret_cast<const void *>(&k_construct_sync_dense);
   if (d.spm_s != 8) return reinterpret_cast<const void *>(&k_construct_sync_spm<0, 64>);
   if (d.cl <= 16) return reinterpret_cast<const void *>(&k_construct_sync_spm<8, 16>);
@@ -3892,26 +4186,31 @@ hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, 
     return e != hipSuccess ? e : mark(ev1);
   }
   if (mode == 0) {
-    const int apb = sync_ants_per_block(d.m);
+    const bool in_lds = memory == 0 && sync_lds(d.n, d.m, d.cl);
+    const int apb = in_lds ? sync_lds_ants_per_block(d.m) : sync_ants_per_block(d.m);
     const int grid = (d.m + apb - 1) / apb;
     Dev dd = d;
     Iter a = it;
     void *args[] = {&dd, &a};
     const void *fn = sync_kernel(d, memory);
-    const bool dbuf = memory == 0 && it.lperiod == 1;
+    const bool dbuf = memory == 0 && (in_lds || it.lperiod == 1);
+    // updates applied to the buffers in turn decide where the last one is
+    const bool odd = in_lds ? ((d.n - 1) / (int)it.lperiod) & 1 : d.n & 1;
+    const int words = in_lds ? 4 * kSyncMaxAnts * grid : 0;
     const dim3 gb((unsigned)(((size_t)d.n * d.ldn + 255) / 256));
     if (dbuf) {
-      hipLaunchKernelGGL(k_sync_buf, gb, dim3(256), 0, s, d, 0);
+      hipLaunchKernelGGL(k_sync_buf, gb, dim3(256), 0, s, d, 0, words);
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
     const hipError_t me = mark(ev0);
     if (me != hipSuccess) return me;
     hipError_t e = hipLaunchCooperativeKernel(fn, dim3(grid), dim3(64 * apb), args,
-                                              lds_bytes(d, 64 * apb), s);
+                                              (in_lds ? (size_t)d.n * d.cl * sizeof(float) : 0) +
+                                                  lds_bytes(d, 64 * apb), s);
     if (e == hipSuccess) e = mark(ev1);
-    if (e != hipSuccess || !dbuf || (d.n & 1) == 0) return e;
-    hipLaunchKernelGGL(k_sync_buf, gb, dim3(256), 0, s, d, 1);
+    if (e != hipSuccess || !dbuf || !odd) return e;
+    hipLaunchKernelGGL(k_sync_buf, gb, dim3(256), 0, s, d, 1, words);
     return hipGetLastError();
   }
   const int apb = kAsyncBlock / 64;

@@ -45,6 +45,26 @@ def test_ants_per_block(acs, m, memory):
     _same(acs, inputs.uniform(61), 2, m=m, cl=12, memory=memory)
 
 
+# pheromone in LDS: up to 1024 ants and 39 K candidate entries (n * cl)
+@pytest.mark.parametrize("n,m,cl,period", [(70, 128, 32, 1), (70, 129, 40, 1), (300, 512, 20, 3),
+                                           (300, 513, 64, 1), (120, 1024, 32, 1),
+                                           (120, 1025, 32, 1), (1220, 33, 31, 1),
+                                           (1221, 33, 32, 1), (40, 7, 4, 1), (200, 50, 3, 250)])
+def test_pheromone_in_lds_and_its_limits(acs, n, m, cl, period):
+    xy = inputs.clustered(n)
+    print(n, m, cl, period, flush=True)
+    col = acs.Colony(xy, seed=3, m=m, cl=cl, local_update_period=period)
+    orc = oracle.Oracle(xy, seed=3, m=m, cl=cl, local_update_period=period)
+    for _ in range(3):
+        col.iterate(1)
+        orc.iterate(1)
+        assert np.array_equal(col.tours(), orc.tours())
+        assert np.array_equal(col.lengths(), orc.lengths())
+        assert np.array_equal(col.tau(), orc.tau())
+    col.close()
+    orc.close()
+
+
 @pytest.mark.parametrize("s,cl", [(8, 16), (8, 17), (8, 40), (3, 16), (16, 33)])
 def test_selective_memory_kernel_shapes(acs, s, cl):
     _same(acs, inputs.uniform(200), 2, m=70, cl=cl, memory=1, spm_s=s)
