@@ -3574,11 +3574,28 @@ __device__ __forceinline__ void argmin_len(const Dev &D, int64_t &bl, int &ba) {
 // A 2-opt move reverses the forward path between its two cities when that
 // path holds at most half the cities, else the rest of the tour; an Or-opt
 // move shifts the shorter of the blocks between the segment's old and new
-// places by L positions and writes the segment into the gap.  One wave per
-// tour, its lanes evaluate the candidates of a move kind at once and the
-// lowest-order improving one is taken, which is the move a sequential scan
-// in that order finds.  Tour, positions and queue live in LDS as 16-bit
-// indices (n <= kLsMaxN); the queue flags are a bitmap.
+// places by L positions and writes the segment into the gap.  Tour, positions
+// and queue live in LDS as 16-bit indices (n <= kLsMaxN); the queue flags are
+// a bitmap.
+//
+// One block per tour.  A popped city is a chain of LDS and distance loads that
+// one wave follows (its lanes evaluate the candidates of a move kind at once
+// and the lowest-order improving one is taken, which is the move a sequential
+// scan in that order finds), and most pops find nothing.  So the waves of a
+// block examine the first cities of the queue at the same time, on the same
+// tour; the first in queue order that has a move is applied by all of them,
+// it and the cities before it are popped, and those after it are examined
+// again on the changed tour: exactly the sequential descent.  A wave gives up
+// its search once a wave before it has found a move.  With few tours that
+// shortens the descent; with many the repeated examinations cost more than
+// they hide, and a tour gets fewer waves.  n = 2392, ms per iteration with the
+// 3-opt moves (2-opt and Or-opt alone), one wave per tour as it was, then 1, 2,
+// 4, 8 and 16 waves; the host takes the starred:
+//   m = 64    16.5 (7.4)   12.9 (7.9)   10.2 (5.8)   7.6 (4.0)   5.9 (3.3)   5.5* (3.4)
+//   m = 400   22.2 (9.6)   18.0 (11.1)  14.0 (8.2)   11.3 (6.4)  10.7* (6.4) 17.6 (11.1)
+//   m = 800   26.2 (11.3)  19.1 (11.6)  16.0 (8.8)   14.4* (8.0) 21.1 (12.8) 35.2 (22.5)
+//   m = 1500  29.6 (12.8)  22.4 (12.8)  19.8* (10.8) 20.9 (11.8) 28.3 (17.3) 56.7 (36.6)
+//   m = 2392  36.1 (18.0)  29.6* (15.7) 38.8 (20.9)  35.8 (19.8) 48.4 (28.5) 91.9 (59.2)
 // ---------------------------------------------------------------------------
 struct LsTour {
   uint16_t *t, *pos, *q;
@@ -3586,7 +3603,11 @@ struct LsTour {
   int n;
 };
 
-__device__ __forceinline__ int ls_wrap(int i, int n) { return ((i % n) + n) % n; }
+// i in [-n, 2n)
+__device__ __forceinline__ int ls_wrap(int i, int n) {
+  i = i < 0 ? i + n : i;
+  return i >= n ? i - n : i;
+}
 __device__ __forceinline__ int ls_at(const LsTour &w, int i) { return w.t[ls_wrap(i, w.n)]; }
 __device__ __forceinline__ void ls_put(const LsTour &w, int i, int c) {
   i = ls_wrap(i, w.n);
@@ -3597,29 +3618,46 @@ __device__ __forceinline__ int ls_dist(const Dev &D, int u, int v) {
   return (int)D.dist[(size_t)u * D.ldn + v];
 }
 
-// queues city c (wave-uniform) unless it is queued; qh, qn wave-uniform
-__device__ __forceinline__ void ls_push(const LsTour &w, int c, int qh, int &qn, int lane) {
-  const uint32_t word = w.inq[c >> 5];
-  if ((word >> (c & 31)) & 1u) return;
-  if (lane == 0) {
-    w.inq[c >> 5] = word | (1u << (c & 31));
-    w.q[(qh + qn) % w.n] = (uint16_t)c;
-  }
-  ++qn;
+// What a wave found for its city: the new positions' description and the
+// cities to queue, in order.
+struct LsMove {
+  int kind;    // 1 reversal of positions i .. j, 2 Or-opt, 3 3-opt
+  int delta;
+  int i, j;    // 1: the shorter side's ends; 2: segment's position and c; 3: pa and boe
+  int L;       // 2: segment length; 3: bod
+  int side;    // 2: placement; 3: reconnection
+  int s0, s1, s2;  // 2: the segment's cities
+  int npush, p0, p1, p2, p3, p4, p5;
+};
+
+// ONE: the block is one wave, whose LDS operations take effect in order; the
+// compiler only has to keep them so.
+template <bool ONE>
+__device__ __forceinline__ void ls_sync() {
+  if (ONE)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  else
+    __syncthreads();
 }
 
-// the forward path from city u to city v reversed, or the rest of the tour
-__device__ __forceinline__ void ls_reverse(const LsTour &w, int u, int v, int lane) {
+// the ends of the forward path from city u to city v, or of the rest of the
+// tour when that is shorter
+__device__ __forceinline__ void ls_shorter(const LsTour &w, int u, int v, int &i, int &j) {
   const int n = w.n;
-  int i = w.pos[u], j = w.pos[v];
-  int len = (j - i + n) % n + 1;
+  i = w.pos[u];
+  j = w.pos[v];
+  const int len = ls_wrap(j - i, n) + 1;
   if (2 * len > n) {
-    const int i2 = (j + 1) % n, j2 = (i - 1 + n) % n;
+    const int i2 = ls_wrap(j + 1, n);
+    j = ls_wrap(i - 1, n);
     i = i2;
-    j = j2;
-    len = n - len;
   }
-  for (int s = lane; s < len / 2; s += 64) {
+}
+
+// the cities at positions i .. j (forward, j reached from i) in reverse order
+__device__ __forceinline__ void ls_reverse_at(const LsTour &w, int i, int j, int tid, int nt) {
+  const int len = ls_wrap(j - i, w.n) + 1;
+  for (int s = tid; s < len / 2; s += nt) {
     const int a = ls_at(w, i + s), b = ls_at(w, j - s);
     ls_put(w, i + s, b);
     ls_put(w, j - s, a);
@@ -3627,60 +3665,47 @@ __device__ __forceinline__ void ls_reverse(const LsTour &w, int u, int v, int la
 }
 
 // block move: positions from .. from + cnt - 1 to from + by .. (by = -L or
-// +L), chunks of 64 ordered so no chunk reads what an earlier chunk wrote
-__device__ __forceinline__ void ls_shift(const LsTour &w, int from, int cnt, int by, int lane) {
-  if (by < 0) {
-    for (int r0 = 0; r0 < cnt; r0 += 64) {
-      const int r = r0 + lane;
-      const int c = r < cnt ? ls_at(w, from + r) : 0;
-      if (r < cnt) ls_put(w, from + r + by, c);
-    }
-  } else {
-    for (int r0 = ((cnt - 1) / 64) * 64; r0 >= 0; r0 -= 64) {
-      const int r = r0 + lane;
-      const int c = r < cnt ? ls_at(w, from + r) : 0;
-      if (r < cnt) ls_put(w, from + r + by, c);
-    }
+// +L), chunks of nt ordered so no chunk reads what an earlier chunk wrote
+template <bool ONE>
+__device__ __forceinline__ void ls_shift(const LsTour &w, int from, int cnt, int by, int tid,
+                                         int nt) {
+  const int chunks = (cnt + nt - 1) / nt;
+  for (int k = 0; k < chunks; ++k) {
+    const int r = (by < 0 ? k : chunks - 1 - k) * nt + tid;
+    const int c = r < cnt ? ls_at(w, from + r) : 0;
+    ls_sync<ONE>();
+    if (r < cnt) ls_put(w, ls_wrap(from + r, w.n) + by, c);
+    ls_sync<ONE>();
   }
 }
 
 // Or-opt: the L cities at positions i .. i + L - 1 (seg, in order) between
 // c and succ(c) (side 0) or reversed between pred(c) and c (side 1)
-__device__ __forceinline__ void ls_oropt(const LsTour &w, int i, int L, int c, int side,
-                                         const int seg[3], int lane) {
-  const int n = w.n;
-  if (side == 0) {
-    const int nb = (w.pos[c] - (i + L) % n + n) % n + 1, nc = n - L - nb;
+template <bool ONE>
+__device__ __forceinline__ void ls_oropt(const LsTour &w, const LsMove &x, int tid, int nt) {
+  const int n = w.n, L = x.L, i = x.i, pc = w.pos[x.j];
+  int place;  // where the segment goes
+  if (x.side == 0) {
+    const int nb = ls_wrap(pc - ls_wrap(i + L, n), n) + 1, nc = n - L - nb;
     if (nb <= nc) {
-      ls_shift(w, i + L, nb, -L, lane);
-      if (lane < L) ls_put(w, i + nb + lane, seg[lane]);
+      ls_shift<ONE>(w, ls_wrap(i + L, n), nb, -L, tid, nt);
+      place = ls_wrap(i + nb, n);
     } else {
-      const int e0 = (w.pos[c] + 1) % n;
-      ls_shift(w, e0, nc, L, lane);
-      if (lane < L) ls_put(w, e0 + lane, seg[lane]);
+      place = ls_wrap(pc + 1, n);
+      ls_shift<ONE>(w, place, nc, L, tid, nt);
     }
   } else {
-    const int c0 = w.pos[c];
-    const int nc = (i - 1 - c0 + 2 * n) % n + 1, nb = n - L - nc;
+    const int nc = ls_wrap(i - 1 - pc, n) + 1, nb = n - L - nc;
     if (nc <= nb) {
-      ls_shift(w, c0, nc, L, lane);
-      if (lane < L) ls_put(w, c0 + lane, seg[L - 1 - lane]);
+      place = pc;
+      ls_shift<ONE>(w, pc, nc, L, tid, nt);
     } else {
-      ls_shift(w, i + L, nb, -L, lane);
-      if (lane < L) ls_put(w, i + nb + lane, seg[L - 1 - lane]);
+      ls_shift<ONE>(w, ls_wrap(i + L, n), nb, -L, tid, nt);
+      place = ls_wrap(i + nb, n);
     }
   }
-}
-
-// the cities at positions i .. j (forward, j reached from i) in reverse order
-__device__ __forceinline__ void ls_reverse_at(const LsTour &w, int i, int j, int lane) {
-  const int n = w.n;
-  const int len = (j - i + n) % n + 1;
-  for (int s = lane; s < len / 2; s += 64) {
-    const int a = ls_at(w, i + s), b = ls_at(w, j - s);
-    ls_put(w, i + s, b);
-    ls_put(w, j - s, a);
-  }
+  const int k = x.side == 0 ? tid : L - 1 - tid;
+  if (tid < L) ls_put(w, place + tid, k == 0 ? x.s0 : k == 1 ? x.s1 : x.s2);
 }
 
 // 3-opt for the popped city a at position pa (local search kind 2): with
@@ -3690,34 +3715,40 @@ __device__ __forceinline__ void ls_reverse_at(const LsTour &w, int i, int j, int
 // c for the four, in candidate order; the second joins b (c for C B') to one
 // of its candidates y, in candidate order, while the partial gain stays
 // positive.  The move a sequential scan finds is the lowest (reconnection,
-// x, y).  The wave takes one x at a time with all four reconnections at once
-// (their loads in one round, the lanes taking y), keeps the first improving
-// move of the most preferred reconnection seen, and stops early once
-// reconnection 0 has one.  Returns true if a move was applied.
+// x, y).  The wave takes one x at a time, two when cl <= 32 (one per half
+// wave), with all four reconnections at once (their loads in one round, the
+// lanes taking y), keeps the first improving move of the most preferred
+// reconnection seen, and stops early once reconnection 0 has one (or a wave
+// before it any move: *found < self).
+template <class F>
 __device__ __forceinline__ bool ls_three_opt(const Dev &D, const LsTour &w, int a, int pa,
-                                          int64_t &len, int qh, int &qn, int lane) {
+                                             uint4 ra, int b, int dab, int lane, const int *found,
+                                             int self, F emit) {
   const int n = w.n, cl = D.cl;
-  const int kl = lane < cl ? lane : cl - 1;
-  const bool cand = lane < cl;
-  const int b = uni(ls_at(w, pa + 1));
-  const int dab = ls_dist(D, a, b);
-  const uint4 ra = D.crec[(size_t)a * cl + kl];
-  const uint4 rb = D.crec[(size_t)b * cl + kl];
+  const int per = cl <= 32 ? 2 : 1;  // x at a time
+  const int half = per == 2 ? lane >> 5 : 0, y = per == 2 ? lane & 31 : lane;
+  const bool cand = y < cl;
+  const uint4 rb = D.crec[(size_t)b * cl + (cand ? y : cl - 1)];
   // a's candidates closer than b: a prefix (the lists are sorted by distance)
   const uint64_t far = __ballot(lane >= cl || !((int)ra.y < dab));
   const int nx = far ? (int)__ffsll((unsigned long long)far) - 1 : 64;
   const int yb = (int)rb.x, dyb = (int)rb.y;  // b's candidates
-  const int oyb = (w.pos[yb] - pa + n) % n;
+  const int oyb = ls_wrap(w.pos[yb] - pa, n);
   int best = 4, bod = 0, boe = 0, bc = 0, bd = 0, be = 0, bf = 0, bdelta = 0;
-  for (int kx = 0; kx < nx && best > 0; ++kx) {
-    const int x = (int)rdlane(ra.x, kx), dax = (int)rdlane(ra.y, kx);
-    const int ox = (w.pos[x] - pa + n) % n;
-    const int px = uni(ls_at(w, pa + ox - 1)), sx = uni(ls_at(w, pa + ox + 1));
+  for (int kx = 0; kx < nx && best > 0; kx += per) {
+    if (self > 0 &&
+        __hip_atomic_load(found, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < self)
+      return false;
+    const int kk = min(kx + half, nx - 1);
+    const bool mine = cand && kx + half < nx;
+    const int x = __shfl((int)ra.x, kk, 64), dax = __shfl((int)ra.y, kk, 64);
+    const int ox = ls_wrap(w.pos[x] - pa, n);
+    const int px = ls_at(w, pa + ox - 1), sx = ls_at(w, pa + ox + 1);
     const int g01 = dab - dax + ls_dist(D, px, x);  // x = d: removed (c, d), c = pred(x)
     const int g23 = dab - dax + ls_dist(D, x, sx);  // x = e or c: removed (x, succ(x))
-    const uint4 rc = D.crec[(size_t)px * cl + kl];  // candidates of c for C B'
+    const uint4 rc = D.crec[(size_t)px * cl + (cand ? y : cl - 1)];  // candidates of c for C B'
     const int yc = (int)rc.x, dyc = (int)rc.y;
-    const int oyc = (w.pos[yc] - pa + n) % n;
+    const int oyc = ls_wrap(w.pos[yc] - pa, n);
 #pragma unroll
     for (int type = 0; type < 4; ++type) {
       if (type >= best) break;
@@ -3725,16 +3756,16 @@ __device__ __forceinline__ bool ls_three_opt(const Dev &D, const LsTour &w, int 
       bool ok;
       if (type == 0) {
         od = ox, oe = oyb;
-        ok = cand && dyb < g01 && ox >= 2 && oyb >= ox;
+        ok = mine && dyb < g01 && ox >= 2 && oyb >= ox;
       } else if (type == 1) {
         od = ox, oe = oyc;
-        ok = cand && dyc < g01 && ox >= 2 && oyc > ox;
+        ok = mine && dyc < g01 && ox >= 2 && oyc > ox;
       } else if (type == 2) {
         od = oyb, oe = ox;
-        ok = cand && dyb < g23 && ox >= 3 && oyb >= 2 && oyb < ox;
+        ok = mine && dyb < g23 && ox >= 3 && oyb >= 2 && oyb < ox;
       } else {
         od = ox + 1, oe = oyb;
-        ok = cand && dyb < g23 && ox >= 2 && ox <= n - 3 && oyb > ox + 1;
+        ok = mine && dyb < g23 && ox >= 2 && ox <= n - 3 && oyb > ox + 1;
       }
       const int c = ls_at(w, pa + od - 1), d = ls_at(w, pa + od);
       const int e = ls_at(w, pa + oe), f = ls_at(w, pa + oe + 1);
@@ -3756,32 +3787,151 @@ __device__ __forceinline__ bool ls_three_opt(const Dev &D, const LsTour &w, int 
     }
   }
   if (best == 4) return false;
-  len += bdelta;
-  // positions pa + 1 .. pa + oe hold B (od - 1 cities) then C
-  const int p0 = (pa + 1) % n, pe = (pa + boe) % n;
-  const int nb = bod - 1, nc = boe - bod + 1;
-  if (best == 3) {
-    ls_reverse_at(w, p0, (p0 + nb - 1) % n, lane);
-    ls_reverse_at(w, (p0 + nb) % n, pe, lane);
-  } else {
-    ls_reverse_at(w, p0, pe, lane);                                 // C' B'
-    if (best <= 1) ls_reverse_at(w, p0, (p0 + nc - 1) % n, lane);   // C
-    if (best != 1) ls_reverse_at(w, (p0 + nc) % n, pe, lane);       // B
-  }
-  ls_push(w, a, qh, qn, lane);
-  ls_push(w, b, qh, qn, lane);
-  ls_push(w, bc, qh, qn, lane);
-  ls_push(w, bd, qh, qn, lane);
-  ls_push(w, be, qh, qn, lane);
-  ls_push(w, bf, qh, qn, lane);
+  emit(LsMove{3, bdelta, pa, boe, bod, best, 0, 0, 0, 6, a, b, bc, bd, be, bf});
   return true;
 }
 
-// One block (one wave) per ant.  Dynamic LDS: t, pos, q (n 16-bit entries
-// each) and the queue bitmap.  kind 2 adds the 3-opt move.
-__global__ __launch_bounds__(64) void k_local_search(Dev D, int kind) {
+// positions pa + 1 .. pa + oe hold B (od - 1 cities) then C
+template <bool ONE>
+__device__ __forceinline__ void ls_apply_three(const LsTour &w, const LsMove &x, int tid, int nt) {
+  const int n = w.n, p0 = ls_wrap(x.i + 1, n), pe = ls_wrap(x.i + x.j, n);
+  const int nb = x.L - 1, nc = x.j - x.L + 1;
+  if (x.side == 3) {
+    ls_reverse_at(w, p0, ls_wrap(p0 + nb - 1, n), tid, nt);
+    ls_reverse_at(w, ls_wrap(p0 + nb, n), pe, tid, nt);
+    return;
+  }
+  ls_reverse_at(w, p0, pe, tid, nt);  // C' B'
+  ls_sync<ONE>();
+  if (x.side <= 1) ls_reverse_at(w, p0, ls_wrap(p0 + nc - 1, n), tid, nt);  // C
+  if (x.side != 1) ls_reverse_at(w, ls_wrap(p0 + nc, n), pe, tid, nt);      // B
+}
+
+// The move the descent makes for city a on the tour as it stands, handed to
+// `emit` where it is found (a struct carried out of the branches would live in
+// scratch memory).  Returns whether there is one.
+template <class F>
+__device__ __forceinline__ bool ls_examine(const Dev &D, const LsTour &w, int a, int kind,
+                                           int lane, const int *found, int self, F emit) {
+  const int n = w.n, cl = D.cl;
+  const uint4 rec = D.crec[(size_t)a * cl + (lane < cl ? lane : cl - 1)];
+  const int c = (int)rec.x, dac = (int)rec.y;
+  const bool cand = lane < cl;
+  const int pa = uni(w.pos[a]);
+  // moves 1 to 3 all read the tour as it stands, so their distances are
+  // loaded together (one round of memory latency); the first improving move
+  // in the order above is then taken
+  const int bs = uni(ls_at(w, pa + 1)), bp = uni(ls_at(w, pa - 1));  // succ, pred of a
+  const int pc = w.pos[c];
+  const int e = ls_at(w, pc + 1), f = ls_at(w, pc - 1);  // succ, pred of c
+  const int dab = ls_dist(D, a, bs), dba = ls_dist(D, bp, a);
+  const int dbe = ls_dist(D, bs, e), dce = ls_dist(D, c, e);
+  const int dbf = ls_dist(D, bp, f), dfc = ls_dist(D, f, c);
+  const int off = ls_wrap(pc - pa, n);
+  int sl[3], xl[3], gl[3], dse[3], dfs[3];  // Or-opt, L = 1, 2, 3
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    sl[i] = uni(ls_at(w, pa + i));      // the segment's last city
+    xl[i] = uni(ls_at(w, pa + i + 1));  // the city after it
+    gl[i] = dba + ls_dist(D, sl[i], xl[i]) - ls_dist(D, bp, xl[i]);
+    dse[i] = ls_dist(D, sl[i], e);
+    dfs[i] = ls_dist(D, f, sl[i]);
+  }
+  // 1. 2-opt on the successor
+  {
+    const int delta = dac + dbe - dab - dce;
+    const uint64_t imp = __ballot(cand && dac < dab && c != bs && e != a && delta < 0);
+    if (imp) {
+      const int k = (int)__ffsll((unsigned long long)imp) - 1;
+      const int cc = (int)rdlane((uint32_t)c, k), ee = (int)rdlane((uint32_t)e, k);
+      int i, j;
+      ls_shorter(w, bs, cc, i, j);
+      emit(LsMove{1, (int)rdlane((uint32_t)delta, k), i, j, 0, 0, 0, 0, 0, 4, a, bs, cc, ee, 0, 0});
+      return true;
+    }
+  }
+  // 2. 2-opt on the predecessor
+  {
+    const int delta = dac + dbf - dba - dfc;
+    const uint64_t imp = __ballot(cand && dac < dba && c != bp && f != a && delta < 0);
+    if (imp) {
+      const int k = (int)__ffsll((unsigned long long)imp) - 1;
+      const int cc = (int)rdlane((uint32_t)c, k), ee = (int)rdlane((uint32_t)f, k);
+      int i, j;
+      ls_shorter(w, a, ee, i, j);
+      emit(LsMove{1, (int)rdlane((uint32_t)delta, k), i, j, 0, 0, 0, 0, 0, 4, a, bp, cc, ee, 0, 0});
+      return true;
+    }
+  }
+  // 3. Or-opt of the segment a .. (L cities)
+#pragma unroll
+  for (int L = 1; L <= 3; ++L) {
+    if (n < L + 3) break;
+    const int x = xl[L - 1], g = gl[L - 1];
+    const bool out = cand && off >= L;
+    const int dA = dac + dse[L - 1] - dce - g;
+    const int dB = dfs[L - 1] + dac - dfc - g;
+    const uint64_t impA = __ballot(out && c != bp && dA < 0);
+    const uint64_t impB = __ballot(out && c != x && dB < 0);
+    if (impA | impB) {
+      const int k = (int)__ffsll((unsigned long long)(impA | impB)) - 1;
+      const int side = ((impA >> k) & 1ull) ? 0 : 1;
+      const int cc = (int)rdlane((uint32_t)c, k);
+      const int ef = (int)rdlane((uint32_t)(side == 0 ? e : f), k);
+      const int delta = (int)rdlane((uint32_t)(side == 0 ? dA : dB), k);
+      emit(LsMove{2, delta, pa, cc, L, side, sl[0], sl[1], sl[2], 6, bp, x, a, sl[L - 1],
+                  side == 0 ? cc : ef, side == 0 ? ef : cc});
+      return true;
+    }
+  }
+  // 4. 3-opt
+  return kind >= 2 && n >= 6 &&
+         ls_three_opt(D, w, a, pa, rec, bs, dab, lane, found, self, emit);
+}
+
+// Pops the first `popped` cities of the queue (its first wave), then queues the
+// move's cities that are not queued, each once, in order (push: lane l holds
+// the l-th of npush).  Returns how many were added.
+__device__ __forceinline__ int ls_requeue(const LsTour &w, int qh, int popped, int left, int push,
+                                          int npush, int lane) {
+  const int n = w.n;
+  if (lane < popped) {
+    const int a = w.q[ls_wrap(qh + lane, n)];
+    __hip_atomic_fetch_and(w.inq + (a >> 5), ~(1u << (a & 31)), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  if (npush == 0) return 0;
+  bool need = lane < npush;
+#pragma unroll
+  for (int u = 0; u < 5; ++u) need = need && !(lane > u && (int)rdlane((uint32_t)push, u) == push);
+  need = need && !((w.inq[push >> 5] >> (push & 31)) & 1u);
+  const uint64_t add = __ballot(need);
+  if (need) {
+    const int at = qh + popped + left + __popcll(add & ((1ull << lane) - 1));
+    w.q[ls_wrap(ls_wrap(at, n), n)] = (uint16_t)push;
+    __hip_atomic_fetch_or(w.inq + (push >> 5), 1u << (push & 31), __ATOMIC_RELAXED,
+                          __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  return __popcll(add);
+}
+
+template <bool ONE>
+__device__ __forceinline__ void ls_apply(const LsTour &w, const LsMove &mv, int tid, int nt) {
+  if (mv.kind == 1) ls_reverse_at(w, mv.i, mv.j, tid, nt);
+  else if (mv.kind == 2) ls_oropt<ONE>(w, mv, tid, nt);
+  else ls_apply_three<ONE>(w, mv, tid, nt);
+}
+
+// One block per ant.  Dynamic LDS: t, pos, q (n 16-bit entries each) and the
+// queue bitmap.  kind 2 adds the 3-opt move.
+constexpr int kLsWaves = 16;
+template <bool ONE>
+__global__ __launch_bounds__(ONE ? 64 : 64 * kLsWaves) void k_local_search(Dev D, int kind) {
   extern __shared__ uint32_t lsm[];
-  const int ant = blockIdx.x, lane = threadIdx.x, n = D.n, cl = D.cl;
+  __shared__ LsMove s_mv[ONE ? 1 : kLsWaves];
+  __shared__ int s_found, s_qn;  // first wave with a move; queued cities
+  const int ant = blockIdx.x, tid = threadIdx.x, nt = ONE ? 64 : blockDim.x, n = D.n;
+  const int lane = tid & 63, wv = ONE ? 0 : uni(tid >> 6), nw = nt >> 6;
   const int np2 = (n + 1) & ~1;  // 16-bit arrays padded to whole words
   LsTour w;
   w.t = reinterpret_cast<uint16_t *>(lsm);
@@ -3791,120 +3941,70 @@ __global__ __launch_bounds__(64) void k_local_search(Dev D, int kind) {
   w.n = n;
   const int W = (n + 31) >> 5;
   const int32_t *tour = D.tours + (size_t)ant * n;
-  for (int p = lane; p < n; p += 64) {
+  for (int p = tid; p < n; p += nt) {
     const int c = tour[p];
     w.t[p] = (uint16_t)c;
     w.pos[c] = (uint16_t)p;
     w.q[p] = (uint16_t)c;
   }
-  for (int k = lane; k < W; k += 64) w.inq[k] = k < W - 1 || (n & 31) == 0 ? ~0u
-                                                            : (1u << (n & 31)) - 1u;
+  for (int k = tid; k < W; k += nt) w.inq[k] = k < W - 1 || (n & 31) == 0 ? ~0u
+                                                             : (1u << (n & 31)) - 1u;
+  if (!ONE && tid == 0) s_found = kLsWaves;
   int qh = 0, qn = n;
   int64_t len = D.lens[ant];
   uint32_t moves = 0;
   const uint32_t cap = 50u * (uint32_t)n;
-  const int kl = lane < cl ? lane : cl - 1;
+  ls_sync<ONE>();
   while (qn > 0 && moves < cap) {
-    const int a = uni(w.q[qh]);
-    qh = (qh + 1) % n;
-    --qn;
-    if (lane == 0) w.inq[a >> 5] &= ~(1u << (a & 31));
-    const uint4 rec = D.crec[(size_t)a * cl + kl];
-    const int c = (int)rec.x, dac = (int)rec.y;
-    const bool cand = lane < cl;
-    const int pa = w.pos[a];
-    // moves 1 to 3 all read the tour as it stands, so their distances are
-    // loaded together (one round of memory latency); the first improving
-    // move in the order above is then applied
-    const int bs = uni(ls_at(w, pa + 1)), bp = uni(ls_at(w, pa - 1));  // succ, pred of a
-    const int pc = w.pos[c];
-    const int e = ls_at(w, pc + 1), f = ls_at(w, pc - 1);  // succ, pred of c
-    const int dab = ls_dist(D, a, bs), dba = ls_dist(D, bp, a);
-    const int dbe = ls_dist(D, bs, e), dce = ls_dist(D, c, e);
-    const int dbf = ls_dist(D, bp, f), dfc = ls_dist(D, f, c);
-    const int off = (pc - pa + n) % n;
-    int sl[3], xl[3], gl[3], dse[3], dfs[3];  // Or-opt, L = 1, 2, 3
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      sl[i] = uni(ls_at(w, pa + i));      // the segment's last city
-      xl[i] = uni(ls_at(w, pa + i + 1));  // the city after it
-      gl[i] = dba + ls_dist(D, sl[i], xl[i]) - ls_dist(D, bp, xl[i]);
-      dse[i] = ls_dist(D, sl[i], e);
-      dfs[i] = ls_dist(D, f, sl[i]);
-    }
-    bool done = false;
-    // 1. 2-opt on the successor
-    {
-      const bool ok = cand && dac < dab && c != bs && e != a;
-      const int delta = dac + dbe - dab - dce;
-      const uint64_t imp = __ballot(ok && delta < 0);
-      if (imp) {
-        const int k = (int)__ffsll((unsigned long long)imp) - 1;
-        const int cc = (int)rdlane((uint32_t)c, k), ee = (int)rdlane((uint32_t)e, k);
-        len += (int)rdlane((uint32_t)delta, k);
-        ls_reverse(w, bs, cc, lane);
-        ls_push(w, a, qh, qn, lane);
-        ls_push(w, bs, qh, qn, lane);
-        ls_push(w, cc, qh, qn, lane);
-        ls_push(w, ee, qh, qn, lane);
-        done = true;
+    int popped = 1;
+    if constexpr (ONE) {
+      int push = 0, npush = 0;
+      moves += ls_examine(D, w, uni(w.q[qh]), kind, lane, nullptr, 0, [&](const LsMove &mv) {
+        push = lane == 0 ? mv.p0 : lane == 1 ? mv.p1 : lane == 2 ? mv.p2 : lane == 3 ? mv.p3
+               : lane == 4 ? mv.p4 : mv.p5;
+        npush = mv.npush;
+        len += mv.delta;
+        ls_apply<true>(w, mv, lane, 64);
+      });
+      qn += ls_requeue(w, qh, 1, qn - 1, push, npush, lane) - 1;
+    } else {
+      const int heads = min(nw, qn);
+      if (wv < heads) {
+        ls_examine(D, w, uni(w.q[ls_wrap(qh + wv, n)]), kind, lane, &s_found, wv,
+                   [&](const LsMove &mv) {
+                     if (lane == 0) {
+                       s_mv[wv] = mv;
+                       atomicMin(&s_found, wv);
+                     }
+                   });
       }
-    }
-    // 2. 2-opt on the predecessor
-    if (!done) {
-      const bool ok = cand && dac < dba && c != bp && f != a;
-      const int delta = dac + dbf - dba - dfc;
-      const uint64_t imp = __ballot(ok && delta < 0);
-      if (imp) {
-        const int k = (int)__ffsll((unsigned long long)imp) - 1;
-        const int cc = (int)rdlane((uint32_t)c, k), ee = (int)rdlane((uint32_t)f, k);
-        len += (int)rdlane((uint32_t)delta, k);
-        ls_reverse(w, a, ee, lane);
-        ls_push(w, a, qh, qn, lane);
-        ls_push(w, bp, qh, qn, lane);
-        ls_push(w, cc, qh, qn, lane);
-        ls_push(w, ee, qh, qn, lane);
-        done = true;
+      __syncthreads();
+      const int first = uni(s_found);
+      popped = min(first + 1, heads);
+      const LsMove &mv = s_mv[first < heads ? first : 0];
+      if (first < heads) {
+        ls_apply<false>(w, mv, tid, nt);
+        len += mv.delta;
+        ++moves;
       }
-    }
-    // 3. Or-opt of the segment a .. (L cities)
-    for (int L = 1; L <= 3 && !done; ++L) {
-      if (n < L + 3) break;
-      const int sL = sl[L - 1], x = xl[L - 1], g = gl[L - 1];
-      const bool out = cand && off >= L;
-      const bool okA = out && c != bp, okB = out && c != x;
-      const int dA = dac + dse[L - 1] - dce - g;
-      const int dB = dfs[L - 1] + dac - dfc - g;
-      const uint64_t impA = __ballot(okA && dA < 0), impB = __ballot(okB && dB < 0);
-      if (impA | impB) {
-        const int k = (int)__ffsll((unsigned long long)(impA | impB)) - 1;
-        const int side = ((impA >> k) & 1ull) ? 0 : 1;
-        const int cc = (int)rdlane((uint32_t)c, k);
-        const int ef = (int)rdlane((uint32_t)(side == 0 ? e : f), k);
-        len += (int)rdlane((uint32_t)(side == 0 ? dA : dB), k);
-        const int seg[3] = {sl[0], sl[1], sl[2]};
-        ls_oropt(w, pa, L, cc, side, seg, lane);
-        ls_push(w, bp, qh, qn, lane);
-        ls_push(w, x, qh, qn, lane);
-        ls_push(w, a, qh, qn, lane);
-        ls_push(w, sL, qh, qn, lane);
-        if (side == 0) {
-          ls_push(w, cc, qh, qn, lane);
-          ls_push(w, ef, qh, qn, lane);
-        } else {
-          ls_push(w, ef, qh, qn, lane);
-          ls_push(w, cc, qh, qn, lane);
+      if (wv == 0) {
+        const int left = qn - popped;
+        const int add = ls_requeue(w, qh, popped, left, (&mv.p0)[min(lane, 5)],
+                                   first < heads ? mv.npush : 0, lane);
+        if (lane == 0) {
+          s_qn = left + add;
+          s_found = kLsWaves;
         }
-        done = true;
       }
+      __syncthreads();
+      qn = uni(s_qn);
     }
-    // 4. 3-opt
-    if (!done && kind >= 2 && n >= 6) done = ls_three_opt(D, w, a, pa, len, qh, qn, lane);
-    if (done) ++moves;
+    qh = ls_wrap(qh + popped, n);
   }
+  ls_sync<ONE>();
   int32_t *out = D.tours + (size_t)ant * n;
-  for (int p = lane; p < n; p += 64) out[p] = w.t[p];
-  if (lane == 0) {
+  for (int p = tid; p < n; p += nt) out[p] = w.t[p];
+  if (tid == 0) {
     D.lens[ant] = len;
     if (moves) atomicAdd(&D.counters[7], (unsigned long long)moves);
   }
@@ -4324,7 +4424,12 @@ int max_sync_ants(const Dev &d, int memory) {
 hipError_t launch_local_search(const Dev &d, int kind, hipStream_t s) {
   const int np2 = (d.n + 1) & ~1;
   const size_t lds = (size_t)3 * np2 * sizeof(uint16_t) + (size_t)((d.n + 31) / 32) * 4;
-  hipLaunchKernelGGL(k_local_search, dim3(d.m), dim3(64), lds, s, d, kind);
+  // waves per tour (see the kernel)
+  const int nw = d.m <= 128 ? 16 : d.m <= 512 ? 8 : d.m <= 1024 ? 4 : d.m <= 1792 ? 2 : 1;
+  if (nw == 1)
+    hipLaunchKernelGGL(k_local_search<true>, dim3(d.m), dim3(64), lds, s, d, kind);
+  else
+    hipLaunchKernelGGL(k_local_search<false>, dim3(d.m), dim3(64 * nw), lds, s, d, kind);
   return hipGetLastError();
 }
 
