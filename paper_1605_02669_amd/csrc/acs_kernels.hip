@@ -1582,20 +1582,43 @@ __global__ __launch_bounds__(256) void k_sync_buf(Dev D, int dir, int words) {
 // Sequential construction, dense memory (Alg. 1 read literally): step by
 // step, and within a step ant by ant, each ant selecting from the pheromone
 // after the local updates of the ants before it in the same step.  One block
-// of kSeqWaves waves.  A round gives the next kSeqWaves unresolved ants of
-// the step one wave each; they select in parallel from the current
-// pheromone.  An ant's choice depends on the pheromone only through the row
-// of its current city, and an ant's update writes rows cur and next, so the
-// round's ants up to (not including) the first whose row an earlier ant of
-// the round writes have made exactly the sequential choices.  They commit
-// (visited bit, tour entry, length, local update; their updates touch
-// disjoint entries); the rest select again in the next round.  Every round
-// commits at least its first ant.  Visited bitmaps live in global memory,
-// since an ant is served by different waves over the iteration.
+// of kSeqWaves waves, kSeqGroup ants of a step at a time.
+//
+// An ant's choice depends on the pheromone only through the row of its
+// current city, and an ant's update writes rows cur and next.  So the ants of
+// a group all choose from the pheromone as it is (ant i on wave i %
+// kSeqWaves); every ant then enters its index at the two rows its choice
+// would write (the least index wins; a table in LDS by city, whose slots
+// cities share when n is larger than it, which can only add a conflict).  The
+// ants before the first whose row an earlier one writes have made exactly the
+// sequential choices: they commit (their updates touch disjoint entries).
+// The others keep their choice unless a committed ant wrote their row, and
+// the entries are made again, without the committed.  Every round commits at
+// least the first ant left.  With 64 ants at n = 2392 a step takes two to
+// three rounds, of which the first alone has all ants to choose.
+//
+// Entering, checking and committing take one thread per ant.  One compute
+// unit's issue slots bound the first round, the barriers and single choices the
+// others.  Rounds of 16 ants, each with its own draws, global reads of the
+// current cities and conflict search, took 11.1 us a step at m = 64 and 461 us
+// at m = n = 2392; this takes 5.5 and 223.  Groups of 64 take 6.1 and 248,
+// groups of 256 choose more often in vain (n = 500, m = 256: 46 us a step
+// against 34; 45 before).
 // ---------------------------------------------------------------------------
 constexpr int kSeqWaves = 16;
+constexpr int kSeqGroup = 128;   // ants choosing at once
+constexpr int kSeqSlots = kSeqGroup / kSeqWaves;  // per wave
+constexpr int kSeqRows = 4096;   // slots of the table of rows (power of two)
+constexpr int kSeqCur = 4096;    // current cities in LDS for up to so many ants
 // visited bitmaps in LDS when all m of them fit in this many words
-constexpr int kSeqLdsWords = 36 * 1024;
+constexpr int kSeqLdsWords = 31 * 1024;
+
+// A choice: next city | (k + 1) << 16 | (kr + 1) << 23 | roulette << 30, k the
+// position of next in cur's list and kr of cur in next's (-1: none).
+__device__ __forceinline__ uint32_t pack_choice(int next, int k, int kr, bool roul) {
+  return (uint32_t)next | (uint32_t)(k + 1) << 16 | (uint32_t)(kr + 1) << 23 |
+         (roul ? 1u << 30 : 0u);
+}
 
 // VIS_LDS: the m visited bitmaps in LDS (dynamic, m * ceil(n/32) words), else
 // in global memory.  In this schedule both entries of an edge always hold
@@ -1604,96 +1627,205 @@ constexpr int kSeqLdsWords = 36 * 1024;
 template <bool VIS_LDS>
 __global__ __launch_bounds__(64 * kSeqWaves) void k_construct_seq_dense(Dev D, Iter A) {
   extern __shared__ uint32_t smem[];
-  __shared__ int s_rows[kSeqWaves][2];  // rows the round's ant w writes (-1: none)
-  __shared__ int s_cur[kSeqWaves];      // current city of the round's ant w (-1: none)
-  const int lane = threadIdx.x & 63;
-  const int wv = threadIdx.x >> 6;
+  __shared__ uint32_t s_rows[kSeqRows];   // round (counted down) << 8 | least ant
+  __shared__ uint32_t s_choice[kSeqGroup];
+  __shared__ float s_val[kSeqGroup];
+  __shared__ uint16_t s_now[kSeqGroup];   // the group's current cities
+  __shared__ uint8_t s_need[kSeqGroup];
+  __shared__ uint16_t s_cur[kSeqCur];
+  __shared__ int s_stop;                  // first ant in conflict
+  const int tid = threadIdx.x, lane = tid & 63, wv = uni(tid >> 6);
   const int n = D.n, m = D.m, cl = D.cl;
   const int W = (n + 31) >> 5;
   const int kl = lane < cl ? lane : cl - 1;
+  const uint64_t clmask = cl >= 64 ? ~0ull : (1ull << cl) - 1;
   uint32_t *const vbase = VIS_LDS ? smem : D.gvis;
+  const bool near = m <= kSeqCur;
 
-  for (int a = wv; a < m; a += kSeqWaves) {
-    uint32_t *vis = vbase + (size_t)a * W;
-    for (int w = lane; w < W; w += 64) vis[w] = 0u;
-    const uint4 draws = philox_batch(A, a, 0, lane);
-    const int start = (int)__umulhi(rdlane(draws.z, 0), (uint32_t)n);
-    if (lane == 0) {
-      vis[start >> 5] |= 1u << (start & 31);
-      D.tours[(size_t)a * n] = start;
-      D.lens[a] = 0;
-    }
+  for (int r = tid; r < kSeqRows; r += 64 * kSeqWaves) s_rows[r] = kNone;
+  for (size_t w = tid; w < (size_t)m * W; w += 64 * kSeqWaves) vbase[w] = 0u;
+  __syncthreads();
+  for (int a = tid; a < m; a += 64 * kSeqWaves) {
+    const uint4 z = philox10(make_uint4(0u, (uint32_t)a, A.it, A.instance), A.key0, A.key1);
+    const int start = (int)__umulhi(z.z, (uint32_t)n);
+    vbase[(size_t)a * W + (start >> 5)] = 1u << (start & 31);
+    D.tours[(size_t)a * n] = start;
+    if (near) s_cur[a] = (uint16_t)start;
   }
   __syncthreads();
-  uint32_t c_greedy = 0, c_roul = 0, c_fb = 0, c_retry = 0;
+  uint32_t c_roul = 0, c_fb = 0;  // per thread (commits)
   uint64_t c_fbu = 0;
+  uint32_t round = 0xfffffe;
+  uint4 draws{};
+  uint32_t left = A.lperiod;
   for (int t = 1; t < n; ++t) {
-    const bool upd = t % (int)A.lperiod == 0;
-    for (int base = 0; base < m;) {
-      const int a = base + wv;
-      const bool act = a < m;
-      Pick p{};
-      int cur = -1, kr = -1;
-      if (act) {
-        uint32_t *vis = vbase + (size_t)a * W;
-        cur = D.tours[(size_t)a * n + t - 1];
-        const uint4 draws = philox_batch(A, a, t & ~63, lane);
-        const uint4 rec = D.crec[(size_t)cur * cl + kl];
-        const Cand c = weigh(D, vis, lane, rec);
-        p = select_dense(D, A, vis, cur, lane, rec, c, draw_of(draws, t));
-        // position of cur in the chosen city's list, for the second entry
-        if (upd) kr = p.k >= 0 ? (int)D.rpos[(size_t)cur * cl + p.k] : cand_pos(D, p.next, cur, lane);
+    const bool upd = --left == 0;
+    if (upd) left = A.lperiod;
+    for (int base = 0; base < m; base += kSeqGroup) {
+      const int g = min(kSeqGroup, m - base);
+      // draws of this wave's ants: lane l holds ant slot l % kSeqSlots at step
+      // (t & ~3) + l / kSeqSlots
+      if (m > kSeqGroup || (t & 3) == 0 || t == 1)
+        draws = philox10(make_uint4((uint32_t)((t & ~3) + lane / kSeqSlots),
+                                    (uint32_t)(base + lane % kSeqSlots * kSeqWaves + wv), A.it,
+                                    A.instance),
+                         A.key0, A.key1);
+      // (one group: its cities are kept up to date where its ants commit)
+      if (t == 1 || m > kSeqGroup) {
+        if (tid < g) {
+          s_now[tid] =
+              near ? s_cur[base + tid] : (uint16_t)D.tours[(size_t)(base + tid) * n + t - 1];
+          s_need[tid] = 1;
+        }
+        if (tid == 0) s_stop = g;
+        __syncthreads();
       }
-      if (lane == 0) {
-        s_cur[wv] = cur;
-        s_rows[wv][0] = act && upd ? cur : -1;
-        s_rows[wv][1] = act && upd ? p.next : -1;
-      }
-      __syncthreads();
-      // the round commits its ants before the first one whose row an earlier
-      // ant of the round writes (every wave finds the same K): lane v holds
-      // ant v's current city and the rows it writes
-      const int vl = lane < kSeqWaves ? lane : kSeqWaves - 1;
-      const int lc = s_cur[vl], lr0 = s_rows[vl][0], lr1 = s_rows[vl][1];
-      bool bad = false;
-#pragma unroll
-      for (int u = 0; u + 1 < kSeqWaves; ++u) {
-        const int r0 = (int)rdlane((uint32_t)lr0, u), r1 = (int)rdlane((uint32_t)lr1, u);
-        bad |= lane > u && lane < kSeqWaves && lc >= 0 && (lc == r0 || lc == r1);
-      }
-      const uint64_t badm = __ballot(bad);
-      const int K = badm ? (int)__ffsll((unsigned long long)badm) - 1 : kSeqWaves;
-      if (act && wv < K) {
-        c_greedy += p.kind == 0;
-        c_roul += p.kind == 1;
-        if (p.kind == 2) { ++c_fb; c_fbu += (uint64_t)(n - t); }
+      auto choose = [&](int i, int sl, uint4 rec, int8_t rpos) {
+        const uint32_t *vis = vbase + (size_t)(base + i) * W;
+        const bool unv = !((vis[rec.x >> 5] >> (rec.x & 31)) & 1u);
+        const uint64_t umask = __ballot(unv) & clmask;
+        uint32_t choice;
+        float val;
+        if (umask) {
+          const float w = unv ? __uint_as_float(rec.w) * __uint_as_float(rec.z) : 0.f;
+          const bool roul = (rdlane(draws.x, sl) >> 8) >= A.q0_24;
+          int k;
+          if (!roul) {
+            // Eq. 1: maximum weight, lowest position
+            const uint32_t wb = __float_as_uint(w);
+            const uint32_t mx = cl <= 32 ? rows_umax_s<32>(wb) : rows_umax_s<64>(wb);
+            k = (int)__builtin_ctzll(__ballot(wb == mx) & umask);
+          } else {
+            // Eq. 2 by roulette, as in pick_candidate
+            float P = w;
+            for (int off = 1; off < cl; off <<= 1) {
+              const float o = __shfl_up(P, off, 64);
+              if (lane >= off) P = P + o;
+            }
+            const float total = __uint_as_float(rdlane(__float_as_uint(P), cl - 1));
+            const float r = ((float)(rdlane(draws.y, sl) >> 8) * 0x1p-24f) * total;
+            const uint64_t sel = __ballot(P > r) & umask;
+            k = sel ? (int)__builtin_ctzll(sel) : 63 - (int)__builtin_clzll(umask);
+          }
+          choice = pack_choice((int)rdlane(rec.x, k), k, (int)rdlane((uint32_t)(int)rpos, k),
+                               roul);
+          val = __uint_as_float(rdlane(rec.w, k));
+        } else {
+          const int cur = uni(s_now[i]);
+          const Pick p = fallback_dense<false>(D, vis, cur, lane, prefix_row(D, cur, lane));
+          choice = pack_choice(p.next, -1, upd ? cand_pos(D, p.next, cur, lane) : -1, false);
+          val = p.tval;
+        }
         if (lane == 0) {
-          __hip_atomic_fetch_or(vbase + (size_t)a * W + (p.next >> 5), 1u << (p.next & 31),
-                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          D.tours[(size_t)a * n + t] = p.next;
-          D.lens[a] += p.d;
+          s_choice[i] = choice;
+          s_val[i] = val;
         }
-        if (upd && lane < 2) {
-          float *h = lane == 0 ? home(D, cur, p.next, p.k) : home(D, p.next, cur, kr);
-          *h = fmaf(A.a_loc, p.tval, A.b_loc);
+      };
+      for (int done = 0; done < g;) {
+        // this wave's ants that choose, two at a time with their rows in flight
+        // together (need: the wave's slots)
+        uint32_t need = (uint32_t)__ballot(lane * kSeqWaves + wv < g &&
+                                           lane * kSeqWaves + wv >= done &&
+                                           s_need[min(lane * kSeqWaves + wv, kSeqGroup - 1)]);
+        while (need) {
+          const int sa = __builtin_ctz(need);
+          need &= need - 1;
+          const int ca = uni(s_now[sa * kSeqWaves + wv]);
+          const uint4 ra = D.crec[(size_t)ca * cl + kl];
+          const int8_t pa = D.rpos[(size_t)ca * cl + kl];
+          if (!need) {
+            choose(sa * kSeqWaves + wv, sa + kSeqSlots * (t & 3), ra, pa);
+            break;
+          }
+          const int sb = __builtin_ctz(need);
+          need &= need - 1;
+          const int cb = uni(s_now[sb * kSeqWaves + wv]);
+          const uint4 rb = D.crec[(size_t)cb * cl + kl];
+          const int8_t pb = D.rpos[(size_t)cb * cl + kl];
+          choose(sa * kSeqWaves + wv, sa + kSeqSlots * (t & 3), ra, pa);
+          choose(sb * kSeqWaves + wv, sb + kSeqSlots * (t & 3), rb, pb);
+        }
+        __syncthreads();
+        // one thread per ant of the group from here
+        const bool mine = tid >= done && tid < g;
+        const int now = mine ? s_now[tid] : 0;
+        const uint32_t choice = mine ? s_choice[tid] : 0u;
+        const int next = (int)(choice & 0xffffu);
+        uint32_t first = kNone;  // the least ant that writes this ant's row
+        if (upd) {
+          if (mine) {
+            const uint32_t key = round << 8 | (uint32_t)tid;
+            atomicMin(&s_rows[now & (kSeqRows - 1)], key);
+            atomicMin(&s_rows[next & (kSeqRows - 1)], key);
+          }
+          __syncthreads();
+          if (mine) {
+            first = s_rows[now & (kSeqRows - 1)] & 255u;
+            if ((int)first < tid) atomicMin(&s_stop, tid);
+          }
+          __syncthreads();
+        }
+        const int stop = s_stop;
+        if (mine && tid < stop) {
+          const int k = (int)((choice >> 16) & 127u) - 1, kr = (int)((choice >> 23) & 127u) - 1;
+          const int a = base + tid;
+          if (upd) {
+            const float x = fmaf(A.a_loc, s_val[tid], A.b_loc);
+            *home(D, now, next, k) = x;
+            *home(D, next, now, kr) = x;
+          }
+          vbase[(size_t)a * W + (next >> 5)] |= 1u << (next & 31);
+          D.tours[(size_t)a * n + t] = next;
+          if (near) s_cur[a] = (uint16_t)next;
+          s_now[tid] = (uint16_t)next;
+          s_need[tid] = 1;
+          c_roul += choice >> 30;
+          if (k < 0) { ++c_fb; c_fbu += (uint64_t)(n - t); }
+        } else if (mine) {
+          s_need[tid] = (int)first < stop;
+        }
+        __syncthreads();
+        if (tid == 0) s_stop = g;
+        done = stop;
+        if (upd && --round == 0) {  // the table's rounds are used up
+          for (int r = tid; r < kSeqRows; r += 64 * kSeqWaves) s_rows[r] = kNone;
+          round = 0xfffffe;
+          __syncthreads();
         }
       }
-      __syncthreads();
-      base += K;
     }
   }
-  // closing edges: lengths and updates (edges shared by several ants get the
+  // lengths, and closing edges' updates (edges shared by several ants get the
   // map once per ant, in any order)
+  uint32_t c_retry = 0;
   for (int a = wv; a < m; a += kSeqWaves) {
-    const int cur = D.tours[(size_t)a * n + n - 1], start = D.tours[(size_t)a * n];
+    const int32_t *tour = D.tours + (size_t)a * n;
+    int64_t len = 0;
+#pragma unroll 4
+    for (int p = lane; p < n; p += 64)
+      len += D.dist[(size_t)tour[p] * D.ldn + tour[p + 1 < n ? p + 1 : 0]];
+#pragma unroll
+    for (int off = 32; off; off >>= 1) len += __shfl_xor(len, off, 64);
+    const int cur = tour[n - 1], start = tour[0];
     const int k1 = cand_pos(D, cur, start, lane);
     const int k2 = cand_pos(D, start, cur, lane);
     float *h = lane == 0 ? home(D, cur, start, k1) : home(D, start, cur, k2);
     if (lane < 2) c_retry += cas_apply(h, __float_as_uint(tau_load(h)), A.a_loc, A.b_loc);
-    if (lane == 0) D.lens[a] += D.dist[(size_t)cur * D.ldn + start];
+    if (lane == 0) D.lens[a] = len;
   }
-  c_retry = (uint32_t)uni((int)(rdlane(c_retry, 0) + rdlane(c_retry, 1)));
-  if (lane == 0) add_counters(D, c_greedy, c_roul, c_fb, c_fbu, c_retry);
+  c_roul = wave_sum_u(c_roul);
+  c_fb = wave_sum_u(c_fb);
+  c_retry = wave_sum_u(c_retry);
+#pragma unroll
+  for (int off = 32; off; off >>= 1)
+    c_fbu += (uint64_t)__shfl_xor((long long)c_fbu, off, 64);
+  if (lane == 0) add_counters(D, 0u, c_roul, c_fb, c_fbu, c_retry);
+  // every step that was neither was greedy
+  if (lane == 0) {
+    const unsigned long long other = (unsigned long long)c_roul + c_fb;
+    const unsigned long long all = wv == 0 ? (unsigned long long)m * (n - 1) : 0ull;
+    atomicAdd(&D.counters[0], all - other);
+  }
 }
 
 // ---------------------------------------------------------------------------
