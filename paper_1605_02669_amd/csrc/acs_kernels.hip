@@ -181,6 +181,31 @@ __device__ __forceinline__ uint32_t rows_umax_s(uint32_t v) {
   return max(m01, max(rdlane(v, 32), rdlane(v, 48)));
 }
 
+// A pointer read from memory (a batch's descriptors) is generic to the
+// compiler, which makes flat accesses of it; they count as LDS operations too.
+// These are all to global memory.
+template <class T>
+__device__ __forceinline__ T *as_global(T *p) {
+  return (T *)(__attribute__((address_space(1))) T *)(uintptr_t)p;
+}
+__device__ __forceinline__ Dev global_dev(const Dev &d) {
+  Dev D = d;
+  D.xy = as_global(d.xy);
+  D.dist = as_global(d.dist);
+  D.crec = as_global(d.crec);
+  D.tau = as_global(d.tau);
+  D.etad = as_global(d.etad);
+  D.rpos = as_global(d.rpos);
+  D.fpre = as_global(d.fpre);
+  D.fbound = as_global(d.fbound);
+  D.ctau = as_global(d.ctau);
+  D.tours = as_global(d.tours);
+  D.lens = as_global(d.lens);
+  D.counters = as_global(d.counters);
+  D.sync = as_global(d.sync);
+  return D;
+}
+
 // Pheromone slot of candidate k in city u's record.
 __device__ __forceinline__ float *cand_tau(const Dev &D, int u, int k) {
   return reinterpret_cast<float *>(const_cast<uint4 *>(D.crec) + (size_t)u * D.cl + k) + 3;
@@ -869,20 +894,20 @@ __global__ __launch_bounds__(256) void k_far_bound(Dev D, Iter A, int ctau_rows)
 // The same for every instance of a batch that has a prefix (blockIdx.y =
 // instance).
 __global__ __launch_bounds__(256) void k_far_bound_batch(const Dev *devs, const Iter *iters) {
-  const Dev &D = devs[blockIdx.y];
+  const Dev D = global_dev(devs[blockIdx.y]);
   const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (D.fpre && i < D.n) far_bound_row(D, iters[blockIdx.y], i, threadIdx.x & 63);
 }
 
 // The same for every instance of a batch (blockIdx.y = instance).
 __global__ __launch_bounds__(256) void k_ctau_in_batch(const Dev *devs) {
-  const Dev D = devs[blockIdx.y];
+  const Dev D = global_dev(devs[blockIdx.y]);
   const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (e < (size_t)D.n * D.cl) D.ctau[e] = __uint_as_float(D.crec[e].w);
 }
 
 __global__ __launch_bounds__(256) void k_ctau_out_batch(const Dev *devs, int canonical) {
-  const Dev D = devs[blockIdx.y];
+  const Dev D = global_dev(devs[blockIdx.y]);
   const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (e < (size_t)D.n * D.cl) ctau_out_slot(D, e, canonical != 0);
 }
@@ -1021,7 +1046,7 @@ __device__ __forceinline__ PrefixRow prefix_row(const Dev &D, int cur, int lane)
 }
 
 // Alg. 2, empty candidate set: greedy over every unvisited city, ties ->
-// lowest index.  With a prefix (D.fpre; pre: cur's), the kFpre cities after
+// lowest index.  With a prefix (D.fpre; pre: cur's, if loaded), the kFpre cities after
 // the candidates come first, two per lane; when the best unvisited one beats
 // D.fbound[cur] strictly, no city beyond the prefix can reach or tie it (the
 // candidates are all visited), so it is the answer of the whole scan.
@@ -1034,14 +1059,14 @@ __device__ __forceinline__ PrefixRow prefix_row(const Dev &D, int cur, int lane)
 // ones and one round ahead made the scan 28 k cycles at n = 2392).
 template <bool COHERENT>
 __device__ __forceinline__ Pick fallback_dense(const Dev &D, const uint32_t *vis, int cur,
-                                               int lane, const PrefixRow &pre,
+                                               int lane, const PrefixRow *pre = nullptr,
                                                const float *tsrc = nullptr) {
   const int n = D.n;
   Pick p;
   const float *trow = (tsrc ? tsrc : D.tau) + (size_t)cur * D.ldn;
   if (D.fpre) {
-    const uint4 pe = pre.e;
-    const float fb = pre.bound;
+    const uint4 pe = pre ? pre->e : D.fpre[(size_t)cur * (kFpre / 2) + lane];
+    const float fb = pre ? pre->bound : D.fbound[cur];
     const uint32_t j0 = pe.x & 0xffffu, j1 = pe.z & 0xffffu;
     const float t0 = COHERENT ? tau_load(trow + j0) : trow[j0];
     const float t1 = COHERENT ? tau_load(trow + j1) : trow[j1];
@@ -1146,12 +1171,12 @@ __device__ __forceinline__ Pick fallback_dense(const Dev &D, const uint32_t *vis
   return p;
 }
 
-// The choice from the current city's records; a fallback loads its prefix.
+// The choice from the current city's records.
 __device__ __forceinline__ Pick select_dense(const Dev &D, const Iter &A, const uint32_t *vis,
                                              int cur, int lane, uint4 rec, Cand c, uint2 q) {
   Pick p;
   const int k = pick_candidate(A, lane, D.cl, c, q, p.kind);
-  if (k < 0) return fallback_dense<false>(D, vis, cur, lane, prefix_row(D, cur, lane));
+  if (k < 0) return fallback_dense<false>(D, vis, cur, lane);
   p.k = k;
   p.next = (int)rdlane(rec.x, k);
   p.d = rdlane(rec.y, k);
@@ -1256,7 +1281,7 @@ __global__ __launch_bounds__(1024) void k_construct_sync_dense(Dev D, Iter A) {
         p.tval = __uint_as_float(rdlane(rec.w, k));
         k2 = (int)rdlane((uint32_t)rpos, k);
       } else {
-        p = fallback_dense<true>(D, vis, cur, lane, pre, rb == 0 ? D.tau : D.tau2);
+        p = fallback_dense<true>(D, vis, cur, lane, &pre, rb == 0 ? D.tau : D.tau2);
         k2 = cand_pos(D, p.next, cur, lane);
       }
       rec = D.crec[(size_t)p.next * cl + kl];
@@ -1452,7 +1477,7 @@ __global__ __launch_bounds__(1024) void k_construct_sync_lds(Dev D, Iter A) {
         d = rdlane(rec.y, x.k);
         val = __uint_as_float(rdlane(tau, x.k));
       } else {
-        const Pick p = fallback_dense<true>(D, vis, cur, lane, pre, rd);
+        const Pick p = fallback_dense<true>(D, vis, cur, lane, &pre, rd);
         x.v = p.next;
         x.kr = cand_pos(D, p.next, cur, lane);
         d = p.d;
@@ -1712,7 +1737,7 @@ __global__ __launch_bounds__(64 * kSeqWaves) void k_construct_seq_dense(Dev D, I
           val = __uint_as_float(rdlane(rec.w, k));
         } else {
           const int cur = uni(s_now[i]);
-          const Pick p = fallback_dense<false>(D, vis, cur, lane, prefix_row(D, cur, lane));
+          const Pick p = fallback_dense<false>(D, vis, cur, lane);
           choice = pack_choice(p.next, -1, upd ? cand_pos(D, p.next, cur, lane) : -1, false);
           val = p.tval;
         }
@@ -2275,7 +2300,7 @@ __device__ __forceinline__ void ant_queued(const Dev &D, const Iter &A, int ant,
         int next, k;
         uint32_t d, tv;
         if (__builtin_expect(umask == 0, 0)) {
-          const Pick p = fallback_dense<false>(D, vis, cur, lane, prefix_row(D, cur, lane));
+          const Pick p = fallback_dense<false>(D, vis, cur, lane);
           next = p.next;
           k = -1;
           d = p.d;
@@ -2403,7 +2428,7 @@ __global__ __launch_bounds__(64 * (kBatchQAnts + 1)) void k_construct_async_batc
   const int b = blockIdx.x;  // the grid has exactly nb blocks
   const int2 item = bitems[b];
   const int inst = uni(item.x);
-  const Dev D = devs[inst];
+  const Dev D = global_dev(devs[inst]);
   const Iter A = iters[inst];
   const QRing q{qsm, qhd, qtl, &qdone};
   if (wv == kBatchQAnts) {
@@ -2433,7 +2458,7 @@ __global__ __launch_bounds__(256) void k_construct_async_batch(const Dev *devs, 
   if (w >= nitems) return;
   const int2 item = items[w];
   const int inst = uni(item.x);
-  const Dev D = devs[inst];
+  const Dev D = global_dev(devs[inst]);
   const Iter A = iters[inst];
   ant_async_dense<ATOMIC>(D, A, uni(item.y), smem + wv * wmax, lane);
 }
@@ -2478,8 +2503,8 @@ __device__ __forceinline__ uint32_t grp_umin(uint32_t v) {
 // This group's bits of a wave ballot.
 template <int L>
 __device__ __forceinline__ uint32_t grp_bits(uint64_t ballot, int base) {
-  const uint32_t b = (uint32_t)(ballot >> base);
-  return L == 32 ? b : (b & 0xffffu);
+  if (L == 32) return base ? (uint32_t)(ballot >> 32) : (uint32_t)ballot;
+  return (uint32_t)(ballot >> base) & 0xffffu;
 }
 
 // Value of v on lane k of this group.
@@ -2487,6 +2512,13 @@ __device__ __forceinline__ uint32_t grp_read(uint32_t v, int base, int k) {
   return (uint32_t)__shfl((int)v, base + k, 64);
 }
 
+// Many ants per SIMD are in flight, so the instructions of a step set the time
+// (256 instances, n in [100, 2000], m = n: 20.8 -> 16.2 ms per
+// construction).  The records come by buffer loads (32-bit offsets; pointers read from
+// memory are generic to the compiler and become flat accesses, which also
+// hold up LDS), an entry's address is computed only where it is updated, the
+// chosen lane marks its own city with the bit it has at hand and keeps its
+// own sum of distances, and lane masks are scalar.
 template <int L, bool ATOMIC>
 __device__ __forceinline__ void ants_async_dense(const Dev &D, const Iter &A, int first,
                                                  uint32_t *vis_wave, int lane) {
@@ -2498,24 +2530,29 @@ __device__ __forceinline__ void ants_async_dense(const Dev &D, const Iter &A, in
   const int kl = gl < cl ? gl : cl - 1;
   const float al = A.a_loc, bl = A.b_loc;
   uint32_t *vis = vis_wave + gi * W;
+  // lanes that hold a candidate, every group
+  const uint64_t cand = __ballot(gl < cl);
+  const __amdgpu_buffer_rsrc_t crs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(D.crec), 0, n * cl * 16, kBufWord3);
+  auto load_rec = [&](int city) {
+    const auto r = __builtin_amdgcn_raw_buffer_load_b128(crs, (city * cl + kl) * 16, 0, 0);
+    return make_uint4(r[0], r[1], r[2], r[3]);
+  };
 
   for (int w = gl; w < W; w += L) vis[w] = 0u;
   uint4 draws = philox10(make_uint4((uint32_t)gl, (uint32_t)ant, A.it, A.instance), A.key0, A.key1);
   const int start = (int)__umulhi(grp_read(draws.z, base, 0), (uint32_t)n);
   if (gl == 0) vis[start >> 5] |= 1u << (start & 31);
   int tb = start;
-  uint4 rec = D.crec[(size_t)start * cl + kl];
+  uint4 rec = load_rec(start);
 
-  int cur = start, prev = -1;
-  float *fwd = nullptr;
-  float fval = 0.f;
-  int64_t len = 0;
-  uint64_t c_kind = 0;  // greedy | roulette << 21 | fallback << 42
-  uint32_t c_retry = 0;
+  int cur = start, prev = -1, kprev = -1;  // kprev: position of cur in prev's list
+  float fval = 0.f;                        // pheromone of (prev, cur) as read
+  uint32_t c_roul = 0, c_fb = 0, c_retry = 0;
   uint64_t c_fbu = 0;
+  uint64_t len = 0;                        // the distances this lane's choices added
   float *pptr = nullptr;
-  unsigned int pexp = 0, pret = 0;
-  bool pend = false;
+  unsigned int pexp = 0, pret = 0;         // equal: nothing to repeat
   uint32_t uleft = A.lperiod;
 
   // chunks of L steps: one Philox batch and one tour store per chunk
@@ -2528,24 +2565,28 @@ __device__ __forceinline__ void ants_async_dense(const Dev &D, const Iter &A, in
   uint32_t clen = 0;
   const int tend = min(t0 + L, n + 1);
   for (int t = t0 > 0 ? t0 : 1; t < tend; ++t) {
-    if (ATOMIC && pend && pret != pexp) c_retry += 1 + cas_apply(pptr, pret, al, bl);
-    pend = false;
-    const uint32_t word = vis[rec.x >> 5];
-    const bool unv = (gl < cl) & !((word >> (rec.x & 31)) & 1u);
+    if (ATOMIC) {
+      if (pret != pexp) c_retry += 1 + cas_apply(pptr, pret, al, bl);
+      pexp = pret;
+    }
+    // (lanes past the list repeat its last candidate: they never win, being
+    // the highest lanes, and the masks leave them out)
+    const uint32_t bit = 1u << (rec.x & 31);
+    uint32_t *const vw = vis + (rec.x >> 5);
+    const bool unv = (*vw & bit) == 0;
     const float w = unv ? __uint_as_float(rec.w) * __uint_as_float(rec.z) : 0.f;
     __asm__ volatile("" ::"v"(w), "v"((int)unv));
     if (t > 1 && --uleft == 0) {
       uleft = A.lperiod;
-      const uint32_t b = grp_bits<L>(__ballot(gl < cl && rec.x == (uint32_t)prev), base);
+      const uint32_t b = grp_bits<L>(__ballot(rec.x == (uint32_t)prev) & cand, base);
       const int kr = b ? __builtin_ctz(b) : -1;
       const float rval = kr >= 0 ? __uint_as_float(grp_read(rec.w, base, kr)) : fval;
-      if (gl < 2 && !map_fixed(gl == 0 ? fval : rval, al, bl)) {
-        float *h = gl == 0 ? fwd : home(D, cur, prev, kr);
-        const float seen = gl == 0 ? fval : rval;
+      const float seen = gl == 0 ? fval : rval;
+      if (gl < 2 && !map_fixed(seen, al, bl)) {
+        float *h = gl == 0 ? home(D, prev, cur, kprev) : home(D, cur, prev, kr);
         if (ATOMIC) {
           pptr = h;
           pexp = __float_as_uint(seen);
-          pend = true;
           pret = atomicCAS(reinterpret_cast<unsigned int *>(h), pexp,
                            __float_as_uint(fmaf(al, seen, bl)));
         } else {
@@ -2554,15 +2595,13 @@ __device__ __forceinline__ void ants_async_dense(const Dev &D, const Iter &A, in
       }
     }
     if (t == n) break;
-    const uint32_t umask = grp_bits<L>(__ballot(unv), base);
-    int next, kind, k = -1;
-    uint32_t d;
+    const uint32_t umask = grp_bits<L>(__ballot(unv) & cand, base);
+    int next, k = -1;
     float tval;
     if (umask) {
       if ((gbits >> (t - t0)) & 1u) {
         const uint32_t mx = grp_umax<L>(__float_as_uint(w));
-        k = __builtin_ctz(grp_bits<L>(__ballot(unv && __float_as_uint(w) == mx), base));
-        kind = 0;
+        k = __builtin_ctz(grp_bits<L>(__ballot(__float_as_uint(w) == mx), base) & umask);
       } else {
         float P = w;
         for (int off = 1; off < cl; off <<= 1) {
@@ -2572,13 +2611,15 @@ __device__ __forceinline__ void ants_async_dense(const Dev &D, const Iter &A, in
         const float total = __uint_as_float(grp_read(__float_as_uint(P), base, cl - 1));
         const uint32_t u24 = grp_read(draws.y, base, t - t0) >> 8;
         const float r = ((float)u24 * 0x1p-24f) * total;
-        const uint32_t sel = grp_bits<L>(__ballot(unv && P > r), base);
+        const uint32_t sel = grp_bits<L>(__ballot(P > r), base) & umask;
         k = sel ? __builtin_ctz(sel) : 31 - __builtin_clz(umask);
-        kind = 1;
+        ++c_roul;
       }
       next = (int)grp_read(rec.x, base, k);
-      d = grp_read(rec.y, base, k);
       tval = __uint_as_float(grp_read(rec.w, base, k));
+      const bool won = gl == k;
+      __hip_atomic_fetch_or(vw, won ? bit : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      clen += won ? rec.y : 0u;
     } else {
       // Alg. 2's fallback over every unvisited city, ties -> lowest index;
       // first over the prefix (as in fallback_dense, 128 / L cities per lane)
@@ -2633,25 +2674,25 @@ __device__ __forceinline__ void ants_async_dense(const Dev &D, const Iter &A, in
       const uint32_t jn = grp_umin<L>((bj != kNone && __float_as_uint(bv) == mx) ? bj : kNone);
       const int owner = __builtin_ctz(grp_bits<L>(__ballot(bj == jn), base));
       next = (int)jn;
-      d = grp_read(bd, base, owner);
       tval = __uint_as_float(grp_read(__float_as_uint(bt), base, owner));
-      kind = 2;
+      if (gl == owner) {
+        mark(vis, next);
+        clen += bd;
+      }
+      ++c_fb;
+      c_fbu += (uint64_t)(n - t);
     }
-    c_kind += 1ull << (21 * kind);
-    if (kind == 2) c_fbu += (uint64_t)(n - t);
-    if (gl == 0) mark(vis, next);
     tb = gl == t - t0 ? next : tb;
-    clen += d;
-    rec = D.crec[(size_t)next * cl + kl];
-    fwd = home(D, cur, next, k);
+    rec = load_rec(next);
     fval = tval;
+    kprev = k;
     prev = cur;
     cur = next;
   }
   len += clen;
   if (t0 < n && gl <= min(L - 1, n - 1 - t0)) D.tours[(size_t)ant * n + t0 + gl] = tb;
   }
-  if (ATOMIC && pend && pret != pexp) c_retry += 1 + cas_apply(pptr, pret, al, bl);
+  if (ATOMIC && pret != pexp) c_retry += 1 + cas_apply(pptr, pret, al, bl);
   {
     const uint32_t b1 = grp_bits<L>(__ballot(gl < cl && D.crec[(size_t)cur * cl + kl].x ==
                                                          (uint32_t)start), base);
@@ -2667,13 +2708,13 @@ __device__ __forceinline__ void ants_async_dense(const Dev &D, const Iter &A, in
                            __HIP_MEMORY_SCOPE_AGENT);
     }
   }
+#pragma unroll
+  for (int off = L / 2; off; off >>= 1) len += (uint64_t)__shfl_xor((long long)len, off, L);
   len += D.dist[(size_t)cur * ldn + start];
   c_retry += grp_read(c_retry, base, 1);
   if (gl == 0) {
-    D.lens[ant] = len;
-    const uint32_t m21 = (1u << 21) - 1;
-    add_counters(D, (uint32_t)c_kind & m21, (uint32_t)(c_kind >> 21) & m21,
-                 (uint32_t)(c_kind >> 42) & m21, c_fbu, c_retry);
+    D.lens[ant] = (int64_t)len;
+    add_counters(D, (uint32_t)(n - 1) - c_roul - c_fb, c_roul, c_fb, c_fbu, c_retry);
   }
 }
 
@@ -2691,7 +2732,7 @@ __global__ __launch_bounds__(256) void k_construct_async_batch_g(const Dev *devs
   if (w >= nw) return;
   const int2 item = witems[w];
   const int inst = uni(item.x);
-  const Dev D = devs[inst];
+  const Dev D = global_dev(devs[inst]);
   const Iter A = iters[inst];
   ants_async_dense<L, ATOMIC>(D, A, uni(item.y), smem + wv * (64 / L) * wmax, lane);
 }
@@ -4163,11 +4204,8 @@ __global__ __launch_bounds__(1024) void k_best(Dev D) {
 // Eq. 4 on the best-so-far tour, dense memory: one wave per tour edge finds
 // both candidate positions with one coalesced load of each row; the 2n
 // directed entries are distinct, so plain read-modify-writes suffice.
-__global__ __launch_bounds__(256) void k_global_dense(Dev D, Iter A) {
-  const int lane = threadIdx.x & 63;
-  const int p = uni(blockIdx.x * 4 + (threadIdx.x >> 6));
+__device__ __forceinline__ void global_edge(const Dev &D, const Iter &A, int p, int lane) {
   const int n = D.n;
-  if (p >= n) return;
   const float ag = A.a_glob;
   const float bg = (float)(A.rho / (double)D.gstate[0]);
   const int u = D.best[p], v = D.best[p + 1 < n ? p + 1 : 0];
@@ -4178,30 +4216,45 @@ __global__ __launch_bounds__(256) void k_global_dense(Dev D, Iter A) {
   }
 }
 
+__global__ __launch_bounds__(256) void k_global_dense(Dev D, Iter A) {
+  const int p = uni(blockIdx.x * 4 + (threadIdx.x >> 6));
+  if (p < D.n) global_edge(D, A, p, threadIdx.x & 63);
+}
+
 // Eq. 4 with the selective memory, in the order of the tour: edge p updates
 // record u_p then record v_p.  City best[p] is touched by edges p-1 and p
 // (edges 0 and n-1 for p = 0), so one wave per tour position applies its
-// record's two updates in that order and no record is shared.
+// record's two updates in that order and no record is shared.  The counters
+// are added once per block of at most 512 (two atomics per position on the same
+// two words took 0.48 ms at n = 20000, now 0.02).
 __global__ __launch_bounds__(256) void k_global_spm(Dev D, Iter A) {
   const int lane = threadIdx.x & 63;
-  const int p = uni(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+  __shared__ uint32_t s_hits, s_misses;
+  if (threadIdx.x == 0) s_hits = s_misses = 0u;
+  __syncthreads();
   const int n = D.n, s = D.spm_s;
-  if (p >= n) return;
+  const int wave = uni(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+  const int waves = gridDim.x * (blockDim.x >> 6);
   const float ag = A.a_glob;
   const float bg = (float)(A.rho / (double)D.gstate[0]);
-  const int r = D.best[p];
-  const int nb1 = p >= 1 ? D.best[p - 1] : D.best[1];
-  const int nb2 = p >= 1 ? D.best[p + 1 < n ? p + 1 : 0] : D.best[n - 1];
-  uint2 pr = spm_record<false>(D, r, lane);
-  uint32_t tail = D.spm_tail[r];
   uint32_t hits = 0, misses = 0;
-  spm_update_wave(pr, tail, s, lane, nb1, ag, bg, A.tau0, hits, misses);
-  spm_update_wave(pr, tail, s, lane, nb2, ag, bg, A.tau0, hits, misses);
-  if (lane < s) D.spm[(size_t)r * s + lane] = pr;
-  if (lane == 0) {
-    D.spm_tail[r] = tail;
-    add_spm_counters(D, hits, misses);
+  for (int p = wave; p < n; p += waves) {
+    const int r = D.best[p];
+    const int nb1 = p >= 1 ? D.best[p - 1] : D.best[1];
+    const int nb2 = p >= 1 ? D.best[p + 1 < n ? p + 1 : 0] : D.best[n - 1];
+    uint2 pr = spm_record<false>(D, r, lane);
+    uint32_t tail = D.spm_tail[r];
+    spm_update_wave(pr, tail, s, lane, nb1, ag, bg, A.tau0, hits, misses);
+    spm_update_wave(pr, tail, s, lane, nb2, ag, bg, A.tau0, hits, misses);
+    if (lane < s) D.spm[(size_t)r * s + lane] = pr;
+    if (lane == 0) D.spm_tail[r] = tail;
   }
+  if (lane == 0) {
+    atomicAdd(&s_hits, hits);
+    atomicAdd(&s_misses, misses);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) add_spm_counters(D, s_hits, s_misses);
 }
 
 // Batched iteration end: block b handles instance b (iteration best and
@@ -4230,25 +4283,14 @@ __global__ __launch_bounds__(1024) void k_best_batch(const Dev *devs, Iter *iter
     for (int p = threadIdx.x; p < n; p += blockDim.x) D.best[p] = D.tours[(size_t)ba * n + p];
 }
 
-// Batched global update (dense): grid (edges / 256, instances).
+// Batched global update (dense), one wave per tour edge as k_global_dense: grid
+// (edges / 4, instances).  (One thread per edge that walks both lists took 121
+// us for 256 instances, n up to 2000; this takes 59.)
 __global__ __launch_bounds__(256) void k_global_batch(const Dev *devs, const Iter *iters) {
-  const Dev D = devs[blockIdx.y];
-  const Iter A = iters[blockIdx.y];
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = D.n;
-  if (p >= n) return;
-  const float ag = A.a_glob;
-  const float bg = (float)(A.rho / (double)D.gstate[0]);
-  const int u = D.best[p], v = D.best[p + 1 < n ? p + 1 : 0];
-  int ku = -1, kv = -1;
-  for (int k = 0; k < D.cl; ++k) {
-    if (D.crec[(size_t)u * D.cl + k].x == (uint32_t)v) ku = k;
-    if (D.crec[(size_t)v * D.cl + k].x == (uint32_t)u) kv = k;
-  }
-  float *h1 = home(D, u, v, ku);
-  float *h2 = home(D, v, u, kv);
-  *h1 = fmaf(ag, *h1, bg);
-  *h2 = fmaf(ag, *h2, bg);
+  const Dev D = global_dev(devs[blockIdx.y]);
+  const int lane = threadIdx.x & 63;
+  const int p = uni(blockIdx.x * 4 + (threadIdx.x >> 6));
+  if (p < D.n) global_edge(D, iters[blockIdx.y], p, lane);
 }
 
 // Best-so-far exchange between the colonies of a batch that all solve one
@@ -4572,7 +4614,7 @@ hipError_t launch_best_global(const Dev &d, const Iter &it, int memory, hipStrea
   if (memory == 0)
     hipLaunchKernelGGL(k_global_dense, dim3((d.n + 3) / 4), dim3(256), 0, s, d, it);
   else
-    hipLaunchKernelGGL(k_global_spm, dim3((d.n + 3) / 4), dim3(256), 0, s, d, it);
+    hipLaunchKernelGGL(k_global_spm, dim3(std::min(512, (d.n + 3) / 4)), dim3(256), 0, s, d, it);
   return hipGetLastError();
 }
 
@@ -4626,7 +4668,7 @@ hipError_t launch_batch_iteration(const Dev *devs, Iter *iters, const int2 *item
     hipLaunchKernelGGL(k_best_batch, dim3(count), dim3(1024), 0, s, devs, iters, flag);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_global_batch, dim3((nmax + 255) / 256, count), dim3(256), 0, s, devs,
+    hipLaunchKernelGGL(k_global_batch, dim3((nmax + 3) / 4, count), dim3(256), 0, s, devs,
                        iters);
     return hipGetLastError();
   }
@@ -4656,7 +4698,7 @@ hipError_t launch_batch_iteration(const Dev *devs, Iter *iters, const int2 *item
   hipLaunchKernelGGL(k_best_batch, dim3(count), dim3(1024), 0, s, devs, iters, flag);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_global_batch, dim3((nmax + 255) / 256, count), dim3(256), 0, s, devs,
+  hipLaunchKernelGGL(k_global_batch, dim3((nmax + 3) / 4, count), dim3(256), 0, s, devs,
                      iters);
   return hipGetLastError();
 }
