@@ -64,10 +64,14 @@ __device__ __forceinline__ unsigned pk2(float a, float b) {
 __device__ __forceinline__ float lo_f(unsigned w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi_f(unsigned w) { return __uint_as_float(w & 0xffff0000u); }
 
-// max(x, 0) as one integer max on the bits: a float with the sign bit set
-// (negative, or -0) is a negative integer and becomes +0
-__device__ __forceinline__ float relu(float x) {
-  return __int_as_float(max(__float_as_int(x), 0));
+// max(x, 0) of two packed bf16 values as one 16-bit integer max of the pair: a
+// value with the sign bit set (negative, or -0) is a negative integer and
+// becomes +0.  Rounding to bf16 keeps the sign, so the maximum comes after it,
+// one instruction for two values where a maximum of each float took two.
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned relu2(unsigned w) {
+  return __builtin_bit_cast(
+      unsigned, __builtin_elementwise_max(__builtin_bit_cast(s16x2, w), (s16x2){0, 0}));
 }
 
 // Inference with everything in registers.  The products are computed
@@ -103,8 +107,9 @@ __device__ __forceinline__ void load_regnet(RegNet &R, const float *P, int lane)
   for (int t = 0; t < 4; ++t) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      const int k = 8 * g + q;
-      R.w1[t][q] = (__bf16)(k < 4 ? P[OW1 + k * H + 16 * t + c16] : 0.f);
+      // read by every lane: behind a branch on g each load waited for the last
+      const float w = q < 4 ? P[OW1 + q * H + 16 * t + c16] : 0.f;
+      R.w1[t][q] = (__bf16)(g == 0 ? w : 0.f);
     }
 #pragma unroll
     for (int b = 0; b < 2; ++b)
@@ -139,15 +144,15 @@ __device__ __forceinline__ float forward16r(const Net &R, float4 x, int lane, u3
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     const f32x4 d = mfma(R.W1(t), bx, R.B1(t));
-    h1[t >> 1][2 * (t & 1)] = pk2(relu(d[0]), relu(d[1]));
-    h1[t >> 1][2 * (t & 1) + 1] = pk2(relu(d[2]), relu(d[3]));
+    h1[t >> 1][2 * (t & 1)] = relu2(pk2(d[0], d[1]));
+    h1[t >> 1][2 * (t & 1) + 1] = relu2(pk2(d[2], d[3]));
   }
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     f32x4 d = mfma(R.W2(t, 0), h1[0], R.B2(t));
     d = mfma(R.W2(t, 1), h1[1], d);
-    h2[t >> 1][2 * (t & 1)] = pk2(relu(d[0]), relu(d[1]));
-    h2[t >> 1][2 * (t & 1) + 1] = pk2(relu(d[2]), relu(d[3]));
+    h2[t >> 1][2 * (t & 1)] = relu2(pk2(d[0], d[1]));
+    h2[t >> 1][2 * (t & 1) + 1] = relu2(pk2(d[2], d[3]));
   }
   f32x4 z = mfma(R.W3(0), h2[0], R.B3());
   z = mfma(R.W3(1), h2[1], z);
@@ -165,7 +170,12 @@ __device__ __forceinline__ float4 load_x(const float *X, int row, int rows) {
 }
 
 // Logits of `rows` feature rows: each wave builds its weight tiles in
-// registers and takes two 16-row tiles per pass.
+// registers and takes two 16-row tiles per pass.  Bound by instruction issue:
+// a pass is 28 matrix instructions (24 us of them at 4.2 M rows) beside about
+// 100 vector ones, most of them the packing and the maxima between layers.
+// 4.2 M rows take 61 us (72 with a maximum per float, branches around the
+// loads, two stores a pass and 1024 blocks), 1000 rows 3.2 us (4.5 with the
+// 16 loads of W1 one after the other).
 constexpr int kFwdWaves = 4;
 
 __global__ __launch_bounds__(64 * kFwdWaves) void k_prior_forward(const float *P, const float *X,
@@ -179,12 +189,15 @@ __global__ __launch_bounds__(64 * kFwdWaves) void k_prior_forward(const float *P
   int r0 = (blockIdx.x * kFwdWaves + wv) * 32;
   float4 xa = load_x(X, r0 + (lane & 15), rows), xb = load_x(X, r0 + 16 + (lane & 15), rows);
   for (; r0 < rows; r0 += stride) {
-    const float4 na = load_x(X, r0 + stride + (lane & 15), rows);
-    const float4 nb = load_x(X, r0 + stride + 16 + (lane & 15), rows);
+    // past the end the last row again, whose logit is not stored: no branch
+    // between the matrix products
+    const int ia = min(r0 + stride + (lane & 15), rows - 1);
+    const int ib = min(r0 + stride + 16 + (lane & 15), rows - 1);
+    const float4 na = *reinterpret_cast<const float4 *>(X + (size_t)ia * 4);
+    const float4 nb = *reinterpret_cast<const float4 *>(X + (size_t)ib * 4);
     const float za = forward16r(R, xa, lane), zb = forward16r(R, xb, lane);
-    const int row = r0 + (lane & 15);
-    if (lane < 16 && row < rows) Z[row] = za;
-    if (lane < 16 && row + 16 < rows) Z[row + 16] = zb;
+    const int row = r0 + (lane & 31);
+    if (lane < 32 && row < rows) Z[row] = lane < 16 ? za : zb;
     xa = na;
     xb = nb;
   }
@@ -557,7 +570,9 @@ hipError_t launch_prior_forward(const float *P, const float *X, int rows, float 
                                 hipStream_t s) {
   const int tiles = (rows + 31) / 32;
   int blocks = (tiles + kFwdWaves - 1) / kFwdWaves;
-  blocks = blocks < 1024 ? (blocks > 0 ? blocks : 1) : 1024;
+  // three blocks per CU are what the registers allow at once (156 a wave): with
+  // a fourth, 256 blocks run alone at the end (4.2 M rows 67.3 us, with three 63.8)
+  blocks = blocks < 768 ? (blocks > 0 ? blocks : 1) : 768;
   hipLaunchKernelGGL(k_prior_forward, dim3(blocks), dim3(64 * kFwdWaves), 0, s, P, X, rows, Z);
   return hipGetLastError();
 }

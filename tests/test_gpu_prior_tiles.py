@@ -1,6 +1,6 @@
-"""The prior's gradient at the edges of its tiles and blocks: waves without
-rows, a last tile of one row, a second pass of the first block's waves; the
-result is added to what the caller's buffers hold."""
+"""The prior's forward pass and gradient at the edges of their tiles and
+blocks: waves without rows, a last tile of one row, a second pass of the first
+block's waves; the gradient is added to what the caller's buffers hold."""
 import numpy as np
 import pytest
 
@@ -44,3 +44,25 @@ def test_gradient_at_tile_edges(acs, rows):
         assert np.linalg.norm(a - b) <= 2e-2 * np.linalg.norm(b) + 2.0**-24 * np.sqrt(b.size), k
     lo = oprior.loss(p, X, Y.astype(np.float64), bf16_ops=True)
     assert abs((L.item() - 8.0) / rows - lo) <= 1e-3 * (1 + abs(lo)) + 8.0 * 2.0**-23 / rows
+
+
+# tiles of 32 rows, 4 waves a block, 768 blocks: 98304 rows are one pass
+@pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 98304 + 17])
+def test_forward_at_tile_edges(acs, rows):
+    import torch
+    from paper_1605_02669_amd import prior
+    g = np.random.default_rng(rows)
+    X = g.uniform(-1, 1, size=(rows, 4)).astype(np.float32)
+    flat = prior.init_params(rows)
+    print("rows", rows, flush=True)
+    P, Xd = torch.tensor(flat, device="cuda"), torch.tensor(X, device="cuda")
+    z = torch.full((rows + 64,), 7.0, dtype=torch.float32, device="cuda")
+    acs._check(acs.load().acs_prior_forward(acs.C.c_void_p(P.data_ptr()),
+                                            acs.C.c_void_p(Xd.data_ptr()), rows,
+                                            acs.C.c_void_p(z.data_ptr()), None))
+    torch.cuda.synchronize()
+    z = z.cpu().numpy()
+    assert np.all(z[rows:] == 7.0)
+    zo, _ = oprior.forward(acs.unpack_prior(flat), X, bf16_ops=True)
+    # as for the random sizes: fp32 sums, bf16 activations that round the other way
+    assert np.all(np.abs(z[:rows] - zo) <= 1e-2 * (1 + np.abs(zo)))
