@@ -46,7 +46,7 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Device buffers of one handle, as offsets into one allocation.
 struct Layout {
-  size_t xy, dist, crec, cand, eta, tau, tau2, etad, rpos, ctau, gvis, fpre, flim, femax, fbound, bflags, spm, spm_tail, xnn, gstart, gcnt, gcity, gxy, upd_rec, upd_nb, upd_next, upd_head, tours, lens,
+  size_t xy, dist, crec, cand, eta, tau, tau2, etad, rpos, ctau, ccnt, gvis, fpre, flim, femax, fbound, bflags, spm, spm_tail, xnn, gstart, gcnt, gcity, gxy, upd_rec, upd_nb, upd_next, upd_head, tours, lens,
       best, gstate, counters, sync, dmax, lnn, total;
   size_t dist_rows;  // rows of the distance matrix `dist` holds at a time
 };
@@ -95,6 +95,7 @@ Layout make_layout(int n, int m, int cl, int ldn, int memory, int s, int mode) {
     L.rpos = take(sizeof(int8_t) * (size_t)n * cl);
     L.ctau = take(sizeof(float) * (size_t)n * cl);
     L.cand = L.ctau;  // while the handle is built; the records keep the lists
+    if (mode == ACS_ASYNC_ATOMIC) L.ccnt = take(sizeof(uint32_t) * (size_t)n * cl);
     if (mode == ACS_SEQUENTIAL) L.gvis = take(sizeof(uint32_t) * (size_t)m * ((n + 31) / 32));
     if (mode == ACS_SYNC) L.tau2 = take(sizeof(float) * (size_t)n * ldn);
     if (fallback_prefix(n, cl)) {
@@ -434,6 +435,7 @@ int init_handle(acs_t *h, const double *coords_xy, int32_t n, const acs_params *
     d.etad = reinterpret_cast<const float *>(w + h->L.etad);
     d.rpos = reinterpret_cast<const int8_t *>(w + h->L.rpos);
     d.ctau = reinterpret_cast<float *>(w + h->L.ctau);
+    if (p->mode == ACS_ASYNC_ATOMIC) d.ccnt = reinterpret_cast<uint32_t *>(w + h->L.ccnt);
     if (p->mode == ACS_SEQUENTIAL) d.gvis = reinterpret_cast<uint32_t *>(w + h->L.gvis);
     if (p->mode == ACS_SYNC) d.tau2 = reinterpret_cast<float *>(w + h->L.tau2);
     if (fallback_prefix(n, h->cl)) {

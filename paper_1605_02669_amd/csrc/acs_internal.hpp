@@ -45,6 +45,9 @@ struct Dev {
                            //   while a construction with an updater wave runs
                            //   (their records then hold the values of the
                            //   iteration's start)
+  uint32_t *ccnt;          // dense, compare-and-swap updates: n x cl, updates of
+                           //   a candidate entry handed to another wave and
+                           //   not applied yet (0 between constructions)
   // selective pheromone memory (Sec. 3.2): the record of city i is s pairs
   // {neighbour (-1 = empty slot), pheromone bits}; spm_tail[i] counts the
   // inserts (the most recently added slot is spm_tail[i] mod s)

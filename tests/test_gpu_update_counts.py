@@ -1,0 +1,60 @@
+"""Compare-and-swap mode with an updater wave: a crossing counted at an edge
+whose owner applies it is neither lost nor applied twice, at the sizes where
+nearly every crossing is counted that way, with a local-update period, and
+over iterations (the counts are back at zero after each)."""
+import numpy as np
+import pytest
+
+import oracle
+from tests import defs
+from paper_1605_02669_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def acs():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1605_02669_amd import acs as mod
+    mod.load()
+    return mod
+
+
+@pytest.mark.parametrize("n,m,cl,period", [(5, 70, 4, 1), (30, 2000, 29, 1), (40, 1500, 3, 1),
+                                           (198, 700, 32, 3)])
+def test_every_crossing_is_applied_once(acs, n, m, cl, period):
+    print("update counts", n, m, cl, period, flush=True)
+    xy = inputs.uniform(n, 17)
+    col = acs.Colony(xy, m=m, cl=cl, mode=acs.ACS_ASYNC_ATOMIC, seed=5, update_path=2,
+                     local_update_period=period)
+    orc = oracle.Oracle(xy, m=1, seed=5)
+    c = orc.constants()
+    strong = 0
+    for _ in range(4):
+        before = col.tau()
+        col.iterate(1)
+        after = col.tau()
+        assert np.array_equal(after, after.T)
+        tours = col.tours().astype(np.int64)
+        a, b = tours, np.roll(tours, -1, axis=1)
+        # edge t of a tour is step t + 1; the closing edge is always updated
+        steps = [t for t in range(n) if (t + 1) % period == 0 or t == n - 1]
+        key = (np.minimum(a, b) * n + np.maximum(a, b))[:, steps]
+        keys, counts = np.unique(key.ravel(), return_counts=True)
+        best, length = col.best()
+        bt = np.asarray(best, dtype=np.int64)
+        nx = np.roll(bt, -1)
+        # Eq. 4's deposit as the library computes it: rho / L_gb in double, then float
+        bg = np.float32(0.1 / length)
+        want = before.copy()
+        for kk, cnt in zip(keys.tolist(), counts.tolist()):
+            u, v = divmod(kk, n)
+            want[u, v] = want[v, u] = orc.local_map_k(before[u, v], cnt)
+            strong += int(before[u, v] != c["tau0"])
+        for u, v in zip(bt.tolist(), nx.tolist()):
+            want[u, v] = want[v, u] = defs.fmaf32(c["a_glob"], want[u, v], bg)
+        assert np.array_equal(after, want), np.argwhere(after != want)[:5]
+    assert strong > n  # entries away from the map's fixed point were crossed
+    col.close()
