@@ -201,6 +201,7 @@ struct acs_t {
   int64_t lnn = 0;
   float tau0 = 0.f;
   uint32_t iter = 0;
+  uint32_t wait_flag = 0;  // the device's flag of an exhausted wait as last read
   double construct_ms = 0.0, iterate_ms = 0.0;
   int construct_launches = 0;
   std::vector<hipEvent_t> ev;
@@ -239,11 +240,11 @@ void release(acs_t *h) {
 
 int sync_and_check(acs_t *h) {
   HIP_TRY(hipStreamSynchronize(h->stream));
-  uint32_t flags[2] = {0, 0};
-  HIP_TRY(hipMemcpy(flags, h->ws + h->L.sync, sizeof flags, hipMemcpyDeviceToHost));
-  if (flags[1])
+  HIP_TRY(hipMemcpy(&h->wait_flag, h->ws + h->L.sync + sizeof(uint32_t), sizeof(uint32_t),
+                    hipMemcpyDeviceToHost));
+  if (h->wait_flag)
     return fail(ACS_E_DEVICE, "a bounded device wait was exhausted (flag %u: 1 grid barrier, "
-                              "2 update ring)", flags[1]);
+                              "2 update ring)", h->wait_flag);
   return ACS_OK;
 }
 
@@ -492,20 +493,24 @@ int iterate_handle(acs_t *h, int32_t k) {
     HIP_TRY(hipEventCreate(&e));
     h->ev.push_back(e);
   }
-  // a bounded wait that ran out in an earlier call was reported by it
-  HIP_TRY(hipMemsetAsync(h->ws + h->L.sync, 0, 2 * sizeof(uint32_t), h->stream));
+  // a bounded wait that ran out in an earlier call was reported by it; after a
+  // call that read the flag as zero there is nothing to clear
+  if (h->wait_flag)
+    HIP_TRY(hipMemsetAsync(h->ws + h->L.sync, 0, 2 * sizeof(uint32_t), h->stream));
+  h->wait_flag = ~0u;  // unknown until it is read
   if (h->timed) HIP_TRY(hipEventRecord(h->ev_begin, h->stream));
+  const int lanes = h->p.lanes_per_ant ? (int)h->p.lanes_per_ant : 64;
   for (int i = 0; i < k; ++i) {
     acs::Iter it = h->base;
     it.it = h->iter + (uint32_t)i;
     HIP_TRY(acs::launch_construct(h->dev, it, (int)h->p.mode, (int)h->p.memory,
-                                  h->p.lanes_per_ant ? (int)h->p.lanes_per_ant : 64,
-                                  queued_kind(h), h->stream,
+                                  lanes, queued_kind(h), h->stream,
                                   h->timed ? h->ev[2 * i] : nullptr,
                                   h->timed ? h->ev[2 * i + 1] : nullptr));
     if (h->p.local_search)
       HIP_TRY(acs::launch_local_search(h->dev, (int)h->p.local_search, h->stream));
-    HIP_TRY(acs::launch_best_global(h->dev, it, (int)h->p.memory, h->stream));
+    HIP_TRY(acs::launch_best_global(h->dev, it, (int)h->p.mode, (int)h->p.memory, lanes,
+                                    queued_kind(h), h->stream));
   }
   if (h->timed) HIP_TRY(hipEventRecord(h->ev_end, h->stream));
   int rc = sync_and_check(h);

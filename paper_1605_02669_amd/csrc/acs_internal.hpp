@@ -169,8 +169,11 @@ inline size_t sync_barrier_words(int m) {
 }
 // Largest m a synchronous launch can keep resident for this instance.
 int max_sync_ants(const Dev &d, int memory);
-hipError_t launch_best_global(const Dev &d, const Iter &it, int memory,
-                              hipStream_t s);
+// The iteration's end: best tours, the candidates' pheromone back in the
+// records where the construction kept it apart, global update.  mode, memory,
+// lanes and queued as given to launch_construct.
+hipError_t launch_best_global(const Dev &d, const Iter &it, int mode, int memory, int lanes,
+                              int queued, hipStream_t s);
 // Local search (2-opt and Or-opt descent; kind 2 adds 3-opt moves) on every
 // ant's tour, dense memory, n <= kLsMaxN; rewrites tours and lengths.
 constexpr int kLsMaxN = 8192;

@@ -851,11 +851,6 @@ __global__ __launch_bounds__(256) void k_ctau_in(Dev D) {
   if (e < (size_t)D.n * D.cl) D.ctau[e] = __uint_as_float(D.crec[e].w);
 }
 
-__global__ __launch_bounds__(256) void k_ctau_out(Dev D, int canonical) {
-  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (e < (size_t)D.n * D.cl) ctau_out_slot(D, e, canonical != 0);
-}
-
 // Before a construction, the bound that lets the dense fallback stop at its
 // prefix.  During a construction an entry only ever receives the local map
 // f(x) = fmaf(a, x, b) of a value one of the edge's entries held (the two
@@ -2064,7 +2059,7 @@ __device__ __forceinline__ void lds_st(uint32_t *p, uint32_t v) {
 // receives every map exactly; the other entry gets the value just written by a
 // device-coherent store, for readers at the other endpoint.  The canonical home is a
 // candidate slot: the one in the record of the smaller city when each city
-// lists the other, else the only one; k_ctau_out copies every canonical
+// lists the other, else the only one; k_best copies every canonical
 // value to its other entry when the construction ends, so both entries
 // then hold exactly the result of all the maps.  An edge with both entries
 // in the dense matrix (a fallback move between cities that do not list each
@@ -4226,7 +4221,16 @@ __global__ __launch_bounds__(ONE ? 64 : 64 * kLsWaves) void k_local_search(Dev D
   }
 }
 
-__global__ __launch_bounds__(1024) void k_best(Dev D) {
+// Block 0: iteration best and best-so-far.  Further blocks, after a construction
+// with an updater wave: the records take their pheromone back from ctau
+// (`canonical` as in ctau_out_slot).  One launch for both, neither fills the
+// chip (4.4 and 4.3 us one after the other, together 4.5).
+__global__ __launch_bounds__(1024) void k_best(Dev D, int canonical) {
+  if (blockIdx.x > 0) {
+    const size_t e = (size_t)(blockIdx.x - 1) * 1024 + threadIdx.x;
+    if (e < (size_t)D.n * D.cl) ctau_out_slot(D, e, canonical != 0);
+    return;
+  }
   __shared__ int s_better;
   int64_t bl;
   int ba;
@@ -4472,6 +4476,11 @@ static const void *sync_kernel(const Dev &d, int memory) {
   return reinterpret_cast<const void *>(&k_construct_sync_spm<8, 64>);
 }
 
+// Whether the construction keeps the candidates' pheromone in ctau.
+static bool updater_dense(int mode, int memory, int lanes, int queued) {
+  return memory == 0 && lanes == 64 && queued && (mode == 1 || mode == 2);
+}
+
 hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, int lanes,
                             int queued, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   // ev0 / ev1 (optional) bracket the construction kernel itself, so that
@@ -4481,7 +4490,7 @@ hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, 
   // value or a value its edge's other entry held from an equal start; the
   // unsynchronised ants that issue their own updates write f(forward value)
   // into a reverse entry that may differ from it, so they scan whole rows
-  const bool queued_dense = memory == 0 && lanes == 64 && queued && (mode == 1 || mode == 2);
+  const bool queued_dense = updater_dense(mode, memory, lanes, queued);
   const bool far = memory == 0 && d.fpre && (mode != 2 || (lanes == 64 && queued));
   if (far) {
     hipLaunchKernelGGL(k_far_bound, dim3((d.n + 3) / 4), dim3(256), 0, s, d, it,
@@ -4559,11 +4568,9 @@ hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, 
     ACS_DENSE_Q(false, false, true)
     ACS_DENSE_Q(false, false, false)
 #undef ACS_DENSE_Q
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = mark(ev1);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_ctau_out, gc, dim3(256), 0, s, d, atomic ? 1 : 0);
-    return hipGetLastError();
+    // (launch_best_global copies ctau back)
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : mark(ev1);
   }
   const hipError_t me = mark(ev0);
   if (me != hipSuccess) return me;
@@ -4650,8 +4657,11 @@ hipError_t launch_local_search(const Dev &d, int kind, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_best_global(const Dev &d, const Iter &it, int memory, hipStream_t s) {
-  hipLaunchKernelGGL(k_best, dim3(1), dim3(1024), 0, s, d);
+hipError_t launch_best_global(const Dev &d, const Iter &it, int mode, int memory, int lanes,
+                              int queued, hipStream_t s) {
+  const unsigned out =
+      updater_dense(mode, memory, lanes, queued) ? (unsigned)((d.n * d.cl + 1023) / 1024) : 0u;
+  hipLaunchKernelGGL(k_best, dim3(1 + out), dim3(1024), 0, s, d, mode == 1 ? 1 : 0);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (memory == 0)
