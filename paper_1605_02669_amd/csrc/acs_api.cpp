@@ -87,15 +87,15 @@ Layout make_layout(int n, int m, int cl, int ldn, int memory, int s, int mode) {
                                                                      (sizeof(uint16_t) * ldn)));
   }
   L.crec = take(sizeof(uint4) * (size_t)n * cl);
-  if (memory == ACS_SPM) L.cand = take(sizeof(int32_t) * (size_t)n * cl);
+  L.cand = take(sizeof(int32_t) * (size_t)n * cl);
   L.eta = take(sizeof(float) * kEtaEntries);
   if (memory == ACS_DENSE) {
     L.tau = take(sizeof(float) * (size_t)n * ldn);
     L.etad = take(sizeof(float) * (size_t)n * ldn);
     L.rpos = take(sizeof(int8_t) * (size_t)n * cl);
     L.ctau = take(sizeof(float) * (size_t)n * cl);
-    L.cand = L.ctau;  // while the handle is built; the records keep the lists
-    if (mode == ACS_ASYNC_ATOMIC) L.ccnt = take(sizeof(uint32_t) * (size_t)n * cl);
+    // the lists are read while the handle is built, the records keep them
+    if (mode == ACS_ASYNC_ATOMIC) L.ccnt = L.cand;
     if (mode == ACS_SEQUENTIAL) L.gvis = take(sizeof(uint32_t) * (size_t)m * ((n + 31) / 32));
     if (mode == ACS_SYNC) L.tau2 = take(sizeof(float) * (size_t)n * ldn);
     if (fallback_prefix(n, cl)) {
@@ -118,7 +118,17 @@ Layout make_layout(int n, int m, int cl, int ldn, int memory, int s, int mode) {
     L.upd_next = take(sizeof(int32_t) * 2 * (size_t)m);
     L.upd_head = take(sizeof(int32_t) * (size_t)n);
   }
-  if (mode == ACS_SYNC) L.bflags = take(sizeof(uint32_t) * acs::sync_barrier_words(m));
+  if (mode == ACS_SYNC) {
+    // the barrier's words: a line per 16 ants, the place of a dense handle's
+    // lists where they need more (up to 1200 ants), a larger region where
+    // that is too small as well
+    const size_t words = sizeof(uint32_t) * acs::sync_barrier_words(m);
+    const size_t lines = 128 * (size_t)((m + 15) / 16 + 1);
+    const bool in_cand =
+        words > lines && memory == ACS_DENSE && words <= sizeof(int32_t) * (size_t)n * cl;
+    L.bflags = take(in_cand ? lines : std::max(lines, words));
+    if (in_cand) L.bflags = L.cand;
+  }
   if (memory == ACS_DENSE) {
     L.tours = take(tour_bytes);
   } else {
