@@ -4451,8 +4451,15 @@ hipError_t launch_fill(const Dev &d, float tau0, uint32_t dmax, bool eta_falls, 
 
 // Ant waves per block of the kernels with an updater wave: the m ants spread
 // evenly over the compute units, two or more blocks per unit, at most
-// kQAnts per block.
-static hipError_t queued_ants_per_block(int m, int *na) {
+// kQAnts per block.  Dense compare-and-swap updates (`counted`): an updater
+// passes over an edge that another one owns, so more of them only shorten the
+// entries' wait: at most two ants share one, three above ten ants per unit, where
+// the updaters' own waves begin to weigh (m = n, us per iteration with as many as
+// the rule allows, with 2, with 3: n = 1500 687, 691, 691; 2000 938, 937, 930;
+// 2392 1222, 1143, 1165; 3000 1609, 1533, 1466; 4000 3568, 3461, 3405; 2000
+// cities and 8000 ants 2962, 2477, 2255).  Plain stores and the selective memory
+// are within noise or slower with fewer.
+static hipError_t queued_ants_per_block(int m, bool counted, int *na) {
   int dev = 0, cus = 256;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -4460,6 +4467,7 @@ static hipError_t queued_ants_per_block(int m, int *na) {
   const int per_cu = (m + cus - 1) / cus;
   const int bpc = std::max(2, (per_cu + kQAnts - 1) / kQAnts);
   *na = std::max(1, std::min(kQAnts, (m + cus * bpc - 1) / (cus * bpc)));
+  if (counted) *na = std::min(*na, per_cu > 10 ? 3 : 2);
   return hipSuccess;
 }
 
@@ -4545,7 +4553,7 @@ hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, 
   const bool atomic = mode == 1;
   if (memory == 0 && lanes == 64 && queued) {
     int na = 0;
-    const hipError_t qe = queued_ants_per_block(d.m, &na);
+    const hipError_t qe = queued_ants_per_block(d.m, atomic, &na);
     if (qe != hipSuccess) return qe;
     const dim3 gq((d.m + na - 1) / na), bq(64 * (na + 1));
     const size_t lq = (size_t)na * kQRing * sizeof(uint4) +
@@ -4600,7 +4608,7 @@ hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, 
     }
   } else if (queued) {
     int na = 0;
-    const hipError_t e = queued_ants_per_block(d.m, &na);
+    const hipError_t e = queued_ants_per_block(d.m, false, &na);
     if (e != hipSuccess) return e;
     const dim3 gq((d.m + na - 1) / na), bq(64 * (na + 1));
     const size_t lq = (size_t)na * kQRing * sizeof(uint4) +
