@@ -2069,7 +2069,7 @@ __device__ __forceinline__ void lds_st(uint32_t *p, uint32_t v) {
 // each of them lets one through per round trip (0.3 us) and sends the others
 // round again: 0.35 repeats per step at n = m = 2392, 5.7 at 198, 7 at 198
 // cities and 1000 ants, where a popular edge set the construction's time.
-// So a crossing is first counted at its home (ccnt): the wave that finds the
+// So (COUNT) a crossing is first counted at its home (ccnt): the wave that finds the
 // count at 0 owns the entry and writes the map of its own and of all the
 // crossings counted meanwhile, until it takes the count back to 0; every other
 // wave is done after its one addition.  The maps are the same function, so the
@@ -2079,12 +2079,16 @@ __device__ __forceinline__ void lds_st(uint32_t *p, uint32_t v) {
 // n = m = 198: 186 -> 111 us, 198 cities and 1000 ants 560 -> 151, n = m = 1000
 // 606 -> 462, 2392 1326 -> 1176; with the count only after a first failed
 // compare-and-swap 116, 235, 476, 1213, after the second 130, 360, 519, 1254.
+// Taken for a local update at every step by at least n / 2 ants; else the edges
+// are too little contended for the count's two extra round trips (n = m = 2392,
+// period 16: 1290 us, 1314 with it; 3000 cities and 256 ants 1228, 1257; 4000 and
+// 2000 the same with both).  A launch counts everywhere or nowhere.
 // Unsynchronised mode (ACS-GPU-Alt, Sec. 3.1.2): each entry is read and its
 // map stored back, both device-coherent but not as one atomic operation;
 // updates landing in between are lost.  (The value the ant read is several
 // steps old by now: storing its map would undo the updates made since.)
 // Returns this lane's retries.
-template <bool ATOMIC>
+template <bool ATOMIC, bool COUNT>
 __device__ __forceinline__ uint32_t apply_entries(const Dev &D, const Iter &A, uint4 e,
                                                   int lane) {
   const bool valid = e.x != kNoEntry;
@@ -2113,11 +2117,11 @@ __device__ __forceinline__ uint32_t apply_entries(const Dev &D, const Iter &A, u
     const bool fwd_canon = k >= 0 && (kr < 0 || u < v);
     float *pc = fwd_canon || both_dense ? pf : pr;
     float *po = fwd_canon || both_dense ? pr : pf;
-    if (both_dense) {
-      unsigned int seen = e.z;
+    if (!COUNT || both_dense) {
+      unsigned int seen = e.z, nw;
       uint32_t r = 0;
       while (true) {
-        const unsigned int nw = __float_as_uint(fmaf(al, __uint_as_float(seen), bl));
+        nw = __float_as_uint(fmaf(al, __uint_as_float(seen), bl));
         const unsigned int old = atomicCAS(reinterpret_cast<unsigned int *>(pc), seen, nw);
         if (old == seen) break;
         seen = old;
@@ -2125,7 +2129,9 @@ __device__ __forceinline__ uint32_t apply_entries(const Dev &D, const Iter &A, u
       }
       // the value the first entry held just before its update is a fresh
       // guess for the second
-      return r + cas_apply(po, seen, al, bl);
+      if (both_dense) return r + cas_apply(po, seen, al, bl);
+      __hip_atomic_store(po, __uint_as_float(nw), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return r;
     }
     // the first wave to count an update of this entry owns it and is its only
     // writer until it has taken the count back to zero
@@ -2165,7 +2171,7 @@ __device__ __forceinline__ uint32_t spm_apply_entries(const Dev &D, const Iter &
 // the wave's own.  SPM: the entries are the selective memory's (see
 // spm_apply_entries; hits and misses count its updates).  Returns this
 // lane's retries.
-template <bool ATOMIC, bool SPM = false>
+template <bool ATOMIC, bool COUNT, bool SPM = false>
 __device__ __forceinline__ uint32_t group_push(const Dev &D, const Iter &A, const QRing &q, int w,
                                                uint32_t &head, uint32_t &tail, bool &direct,
                                                int lane, uint4 e, int t0, int g1,
@@ -2189,7 +2195,7 @@ __device__ __forceinline__ uint32_t group_push(const Dev &D, const Iter &A, cons
     head = (uint32_t)g1;
     const uint4 own = mine ? e : make_uint4(kNoEntry, 0u, 0u, 0u);
     if (SPM) return spm_apply_entries<ATOMIC>(D, A, own, hits, misses);
-    return apply_entries<ATOMIC>(D, A, own, lane);
+    return apply_entries<ATOMIC, COUNT>(D, A, own, lane);
   }
   if (mine) q.ent[(size_t)w * kQRing + ((lane + t0) & (kQRing - 1))] = e;
   head = (uint32_t)g1;
@@ -2204,7 +2210,7 @@ __device__ __forceinline__ uint32_t group_push(const Dev &D, const Iter &A, cons
 // from its tail), and applies them together, so the updates of different
 // rings share their memory round trips.  With nothing pending it sleeps, so
 // it takes few issue slots from the ant waves that share its SIMD.
-template <bool ATOMIC, bool SPM = false, int NR = kQAnts>
+template <bool ATOMIC, bool COUNT, bool SPM = false, int NR = kQAnts>
 __device__ __forceinline__ void ring_updater(const Dev &D, const Iter &A, const QRing &q,
                                              int lane, int na) {
   static_assert((kQRing & (kQRing - 1)) == 0 && kQRing >= 64 + kQGroup, "ring size");
@@ -2237,7 +2243,7 @@ __device__ __forceinline__ void ring_updater(const Dev &D, const Iter &A, const 
       if (SPM)
         retries += spm_apply_entries<ATOMIC>(D, A, e, hits, misses);
       else
-        retries += apply_entries<ATOMIC>(D, A, e, lane);
+        retries += apply_entries<ATOMIC, COUNT>(D, A, e, lane);
       idle = 0;
       continue;
     }
@@ -2273,7 +2279,7 @@ __device__ __forceinline__ void ring_updater(const Dev &D, const Iter &A, const 
 // the per-step test drops out.  Decisions are the same as those of
 // ant_async_dense.
 // ---------------------------------------------------------------------------
-template <bool ATOMIC, bool HALF, bool EVERY = false>
+template <bool ATOMIC, bool HALF, bool EVERY = false, bool COUNT = false>
 __device__ __forceinline__ void ant_queued(const Dev &D, const Iter &A, int ant, uint32_t *vis,
                                            int lane, const QRing &q, int qw) {
   const int n = D.n, cl = D.cl;
@@ -2387,7 +2393,7 @@ __device__ __forceinline__ void ant_queued(const Dev &D, const Iter &A, int ant,
         clen += d;
         cur = next;
       }
-      c_retry += group_push<ATOMIC>(D, A, q, qw, qhead, qtail, qdirect, lane, e, t0, g1, unused,
+      c_retry += group_push<ATOMIC, COUNT>(D, A, q, qw, qhead, qtail, qdirect, lane, e, t0, g1, unused,
                                     unused);
       g0 = g1;
     }
@@ -2402,7 +2408,7 @@ __device__ __forceinline__ void ant_queued(const Dev &D, const Iter &A, int ant,
     const uint32_t x = rdlane(__float_as_uint(tau_load(qhome(D, cur, start, k1))), 0);
     const uint4 ce =
         make_uint4((uint32_t)cur | ((uint32_t)start << 16), (uint32_t)k1, x, (uint32_t)k2);
-    c_retry += group_push<ATOMIC>(D, A, q, qw, qhead, qtail, qdirect, lane, ce, n, n + 1, unused,
+    c_retry += group_push<ATOMIC, COUNT>(D, A, q, qw, qhead, qtail, qdirect, lane, ce, n, n + 1, unused,
                                   unused);
     len += D.dist[(size_t)cur * D.ldn + start];
   }
@@ -2418,7 +2424,7 @@ __device__ __forceinline__ void ant_queued(const Dev &D, const Iter &A, int ant,
 // host picks na so that every compute unit holds about the same number of
 // ants (the slowest unit sets the iteration time).  Dynamic LDS: the rings
 // of the na ant waves, then their visited bitmaps.
-template <bool ATOMIC, bool HALF, bool EVERY>
+template <bool ATOMIC, bool HALF, bool EVERY, bool COUNT = false>
 __global__ __launch_bounds__(64 * (kQAnts + 1)) void k_construct_async_dense_q(Dev D, Iter A) {
   extern __shared__ uint4 qsm[];
   __shared__ uint32_t qhd[kQAnts], qtl[kQAnts], qdone;
@@ -2433,13 +2439,13 @@ __global__ __launch_bounds__(64 * (kQAnts + 1)) void k_construct_async_dense_q(D
   __syncthreads();
   const QRing q{qsm, qhd, qtl, &qdone};
   if (wv == na) {
-    ring_updater<ATOMIC>(D, A, q, lane, na);
+    ring_updater<ATOMIC, COUNT>(D, A, q, lane, na);
     return;
   }
   uint32_t *vis = reinterpret_cast<uint32_t *>(qsm + (size_t)na * kQRing) +
                   wv * ((D.n + 31) >> 5);
   const int ant = uni(blockIdx.x * na + wv);
-  if (ant < D.m) ant_queued<ATOMIC, HALF, EVERY>(D, A, ant, vis, lane, q, wv);
+  if (ant < D.m) ant_queued<ATOMIC, HALF, EVERY, COUNT>(D, A, ant, vis, lane, q, wv);
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   if (lane == 0) atomicAdd(&qdone, 1u);
 }
@@ -2470,7 +2476,7 @@ __global__ __launch_bounds__(64 * (kBatchQAnts + 1)) void k_construct_async_batc
   const Iter A = iters[inst];
   const QRing q{qsm, qhd, qtl, &qdone};
   if (wv == kBatchQAnts) {
-    ring_updater<ATOMIC>(D, A, q, lane, kBatchQAnts);
+    ring_updater<ATOMIC, false>(D, A, q, lane, kBatchQAnts);
     return;
   }
   uint32_t *vis = reinterpret_cast<uint32_t *>(qsm + (size_t)kBatchQAnts * kQRing) +
@@ -3683,7 +3689,7 @@ __device__ __forceinline__ void spm_ant_queued(const Dev &D, const Iter &A, int 
         prev = cur;
         cur = next;
       }
-      c_retry += group_push<ATOMIC, true>(D, A, q, qw, qhead, qtail, qdirect, lane, e, t0, g1,
+      c_retry += group_push<ATOMIC, false, true>(D, A, q, qw, qhead, qtail, qdirect, lane, e, t0, g1,
                                           hits, misses);
       g0 = g1;
     }
@@ -3695,7 +3701,7 @@ __device__ __forceinline__ void spm_ant_queued(const Dev &D, const Iter &A, int 
     const uint4 ce = lane == 0 ? make_uint4((uint32_t)cur, arrived_upd ? (uint32_t)prev : kNone,
                                             (uint32_t)start, 0u)
                                : make_uint4((uint32_t)start, nb_start, (uint32_t)cur, 0u);
-    c_retry += group_push<ATOMIC, true>(D, A, q, qw, qhead, qtail, qdirect, lane, ce, n, n + 2,
+    c_retry += group_push<ATOMIC, false, true>(D, A, q, qw, qhead, qtail, qdirect, lane, ce, n, n + 2,
                                         hits, misses);
     len += dist_xy(D, cur, start);
   }
@@ -3728,7 +3734,7 @@ __global__ __launch_bounds__(64 * (kQAnts + 1)) void k_construct_async_spm_q(Dev
   __syncthreads();
   const QRing q{qsm, qhd, qtl, &qdone};
   if (wv == na) {
-    ring_updater<ATOMIC, true>(D, A, q, lane, na);
+    ring_updater<ATOMIC, false, true>(D, A, q, lane, na);
     return;
   }
   uint32_t *vis = reinterpret_cast<uint32_t *>(qsm + (size_t)na * kQRing) + wv * D.vw;
@@ -4553,7 +4559,11 @@ hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, 
   const bool atomic = mode == 1;
   if (memory == 0 && lanes == 64 && queued) {
     int na = 0;
-    const hipError_t qe = queued_ants_per_block(d.m, atomic, &na);
+    const bool every = it.lperiod == 1;
+    // crossings counted at their edge (apply_entries): where at least half as
+    // many ants as cities update at every step
+    const bool counted = atomic && every && 2 * d.m >= d.n;
+    const hipError_t qe = queued_ants_per_block(d.m, counted, &na);
     if (qe != hipSuccess) return qe;
     const dim3 gq((d.m + na - 1) / na), bq(64 * (na + 1));
     const size_t lq = (size_t)na * kQRing * sizeof(uint4) +
@@ -4563,18 +4573,19 @@ hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, 
     if (!far) hipLaunchKernelGGL(k_ctau_in, gc, dim3(256), 0, s, d);
     const hipError_t me = mark(ev0);
     if (me != hipSuccess) return me;
-    const bool every = it.lperiod == 1;
-#define ACS_DENSE_Q(AT, HF, EV)                                                        \
-    if (atomic == AT && half == HF && every == EV)                                      \
-      hipLaunchKernelGGL((k_construct_async_dense_q<AT, HF, EV>), gq, bq, lq, s, d, it);
-    ACS_DENSE_Q(true, true, true)
-    ACS_DENSE_Q(true, true, false)
-    ACS_DENSE_Q(true, false, true)
-    ACS_DENSE_Q(true, false, false)
-    ACS_DENSE_Q(false, true, true)
-    ACS_DENSE_Q(false, true, false)
-    ACS_DENSE_Q(false, false, true)
-    ACS_DENSE_Q(false, false, false)
+#define ACS_DENSE_Q(AT, HF, EV, CT)                                                    \
+    if (atomic == AT && half == HF && every == EV && counted == CT)                     \
+      hipLaunchKernelGGL((k_construct_async_dense_q<AT, HF, EV, CT>), gq, bq, lq, s, d, it);
+    ACS_DENSE_Q(true, true, true, true)
+    ACS_DENSE_Q(true, false, true, true)
+    ACS_DENSE_Q(true, true, true, false)
+    ACS_DENSE_Q(true, true, false, false)
+    ACS_DENSE_Q(true, false, true, false)
+    ACS_DENSE_Q(true, false, false, false)
+    ACS_DENSE_Q(false, true, true, false)
+    ACS_DENSE_Q(false, true, false, false)
+    ACS_DENSE_Q(false, false, true, false)
+    ACS_DENSE_Q(false, false, false, false)
 #undef ACS_DENSE_Q
     // (launch_best_global copies ctau back)
     const hipError_t e = hipGetLastError();

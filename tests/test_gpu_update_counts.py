@@ -1,7 +1,8 @@
 """Compare-and-swap mode with an updater wave: a crossing counted at an edge
 whose owner applies it is neither lost nor applied twice, at the sizes where
-nearly every crossing is counted that way, with a local-update period, and
-over iterations (the counts are back at zero after each)."""
+nearly every crossing is counted that way and over iterations (the counts are
+back at zero after each); the same on both sides of the rule that takes the
+counts (half as many ants as cities, an update at every step)."""
 import numpy as np
 import pytest
 
@@ -23,6 +24,7 @@ def acs():
 
 
 @pytest.mark.parametrize("n,m,cl,period", [(5, 70, 4, 1), (30, 2000, 29, 1), (40, 1500, 3, 1),
+                                           (198, 99, 32, 1), (198, 98, 32, 1),
                                            (198, 700, 32, 3)])
 def test_every_crossing_is_applied_once(acs, n, m, cl, period):
     print("update counts", n, m, cl, period, flush=True)
