@@ -26,6 +26,7 @@
 #include <climits>
 
 #include "acs_internal.hpp"
+#include "acs_protocol.hpp"
 
 namespace acs {
 namespace {
@@ -4146,7 +4147,7 @@ template <bool ONE>
 __global__ __launch_bounds__(ONE ? 64 : 64 * kLsWaves) void k_local_search(Dev D, int kind) {
   extern __shared__ uint32_t lsm[];
   __shared__ LsMove s_mv[ONE ? 1 : kLsWaves];
-  __shared__ int s_found, s_qn;  // first wave with a move; queued cities
+  __shared__ int s_found[2], s_qn;  // first wave with a move (queue_round); queued cities
   const int ant = blockIdx.x, tid = threadIdx.x, nt = ONE ? 64 : blockDim.x, n = D.n;
   const int lane = tid & 63, wv = ONE ? 0 : uni(tid >> 6), nw = nt >> 6;
   const int np2 = (n + 1) & ~1;  // 16-bit arrays padded to whole words
@@ -4166,8 +4167,9 @@ __global__ __launch_bounds__(ONE ? 64 : 64 * kLsWaves) void k_local_search(Dev D
   }
   for (int k = tid; k < W; k += nt) w.inq[k] = k < W - 1 || (n & 31) == 0 ? ~0u
                                                              : (1u << (n & 31)) - 1u;
-  if (!ONE && tid == 0) s_found = kLsWaves;
+  if (!ONE && tid < 2) s_found[tid] = kNoWave;
   int qh = 0, qn = n;
+  uint32_t round = 0;
   int64_t len = D.lens[ant];
   uint32_t moves = 0;
   const uint32_t cap = 50u * (uint32_t)n;
@@ -4186,34 +4188,32 @@ __global__ __launch_bounds__(ONE ? 64 : 64 * kLsWaves) void k_local_search(Dev D
       qn += ls_requeue(w, qh, 1, qn - 1, push, npush, lane) - 1;
     } else {
       const int heads = min(nw, qn);
-      if (wv < heads) {
-        ls_examine(D, w, uni(w.q[ls_wrap(qh + wv, n)]), kind, lane, &s_found, wv,
+      auto examine = [&](int *found) {
+        ls_examine(D, w, uni(w.q[ls_wrap(qh + wv, n)]), kind, lane, found, wv,
                    [&](const LsMove &mv) {
                      if (lane == 0) {
                        s_mv[wv] = mv;
-                       atomicMin(&s_found, wv);
+                       atomicMin(found, wv);
                      }
                    });
-      }
-      __syncthreads();
-      const int first = uni(s_found);
-      popped = min(first + 1, heads);
-      const LsMove &mv = s_mv[first < heads ? first : 0];
-      if (first < heads) {
-        ls_apply<false>(w, mv, tid, nt);
-        len += mv.delta;
-        ++moves;
-      }
-      if (wv == 0) {
-        const int left = qn - popped;
-        const int add = ls_requeue(w, qh, popped, left, (&mv.p0)[min(lane, 5)],
-                                   first < heads ? mv.npush : 0, lane);
-        if (lane == 0) {
-          s_qn = left + add;
-          s_found = kLsWaves;
+      };
+      auto act = [&](int found) {
+        const int first = uni(found);
+        popped = min(first + 1, heads);
+        const LsMove &mv = s_mv[first < heads ? first : 0];
+        if (first < heads) {
+          ls_apply<false>(w, mv, tid, nt);
+          len += mv.delta;
+          ++moves;
         }
-      }
-      __syncthreads();
+        if (wv == 0) {
+          const int left = qn - popped;
+          const int add = ls_requeue(w, qh, popped, left, (&mv.p0)[min(lane, 5)],
+                                     first < heads ? mv.npush : 0, lane);
+          if (lane == 0) s_qn = left + add;
+        }
+      };
+      queue_round(s_found, round++, wv, heads, [] { __syncthreads(); }, examine, act);
       qn = uni(s_qn);
     }
     qh = ls_wrap(qh + popped, n);
