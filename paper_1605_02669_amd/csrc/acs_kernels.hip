@@ -4535,7 +4535,7 @@ hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, 
     const void *fn = sync_kernel(d, memory);
     const bool dbuf = memory == 0 && (in_lds || it.lperiod == 1);
     // updates applied to the buffers in turn decide where the last one is
-    const bool odd = in_lds ? ((d.n - 1) / (int)it.lperiod) & 1 : d.n & 1;
+    const bool odd = in_lds ? ((uint32_t)(d.n - 1) / it.lperiod) & 1 : d.n & 1;
     const int words = in_lds ? 4 * kSyncMaxAnts * grid : 0;
     const dim3 gb((unsigned)(((size_t)d.n * d.ldn + 255) / 256));
     if (dbuf) {
