@@ -292,11 +292,8 @@ __device__ __forceinline__ int cand_pos(const Dev &D, int u, int v, int lane) {
 // agent-coherent loads for everything the updates touch, so no cache
 // write-back or invalidation is needed.
 //
-// Epochs are (iteration << 17 | barrier number), modulo 2^32 (a construction
-// has fewer than 2^17 barriers), and a wait is for "at least" by the sign of
-// the difference: every flag was last written in this construction or the one
-// before it.  The waits are bounded: on exhaustion an error flag is raised,
-// later waits no longer poll, and the kernel runs to its end.
+// The waits are bounded: on exhaustion an error flag is raised, later waits no
+// longer poll, and the kernel runs to its end.  (Epochs: see barrier_reached.)
 //
 // Dev::bflags holds, per XCD (8), a list of one arrival epoch per block of the
 // grid and a mailbox of 8 epochs (one per XCD), in 128-byte lines of their
@@ -307,12 +304,9 @@ struct GridBar {       // the first wave's
   bool leader;
 };
 
-__device__ __forceinline__ uint32_t barrier_epoch(const Iter &A, uint32_t bar) {
-  return A.it << 17 | bar;
-}
 __device__ __forceinline__ bool reached(const uint32_t *flag, uint32_t epoch) {
-  return (int32_t)(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - epoch) >=
-         0;
+  return barrier_reached(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                         epoch);
 }
 
 // Polls until `done` holds on every lane of the wave; false when the wait
@@ -346,7 +340,7 @@ __device__ __forceinline__ GridBar grid_join(const Dev &D, const Iter &A) {
   // HW_REG_XCC_ID, its low three bits
   const uint32_t x = (uint32_t)__builtin_amdgcn_s_getreg(20 | (2 << 11));
   uint32_t *tab = D.bflags + kXcds * xcd_words();
-  const uint32_t tag = (A.it + 1) << 4 | 8;  // never 0, other than the last iteration's
+  const uint32_t tag = (A.it + 1) << 4 | 8;  // no other iteration's, nor a cleared word
   if (lane == 0)
     __hip_atomic_store(tab + self, tag | x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   uint32_t rank = 0, members = 0, xcds = 0;
@@ -1326,19 +1320,19 @@ __global__ __launch_bounds__(1024) void k_construct_sync_dense(Dev D, Iter A) {
         pk2 = k2;
         pval = p.tval;
       }
-      grid_barrier_f(D, gbar, barrier_epoch(A, ++bar));
+      grid_barrier_f(D, gbar, barrier_epoch(A.it, ++bar));
     } else if (t % A.lperiod == 0) {
-      grid_barrier_f(D, gbar, barrier_epoch(A, ++bar));
+      grid_barrier_f(D, gbar, barrier_epoch(A.it, ++bar));
       if (active) {
         float *h = lane == 0 ? home(D, cur, p.next, p.k) : home(D, p.next, cur, k2);
         if (lane < 2 && !map_fixed(p.tval, A.a_loc, A.b_loc))
           c_retry += cas_apply(h, __float_as_uint(p.tval), A.a_loc, A.b_loc);
       }
-      if (t + 1 < n) grid_barrier_f(D, gbar, barrier_epoch(A, ++bar));
+      if (t + 1 < n) grid_barrier_f(D, gbar, barrier_epoch(A.it, ++bar));
     }
     if (active) cur = p.next;
   }
-  if (!dbuf && (n - 1) % A.lperiod != 0) grid_barrier_f(D, gbar, barrier_epoch(A, ++bar));
+  if (!dbuf && (n - 1) % A.lperiod != 0) grid_barrier_f(D, gbar, barrier_epoch(A.it, ++bar));
   if (active) {
     // closing edge: its length and, as the last step's crossings, its update
     len += D.dist[(size_t)cur * D.ldn + start];
@@ -1587,6 +1581,13 @@ __global__ __launch_bounds__(1024) void k_construct_sync_lds(Dev D, Iter A) {
       add_counters(D, (uint32_t)(n - 1) - c_roul - c_fb, c_roul, c_fb, c_fbu, c_retry);
     }
   }
+}
+
+// The grid barrier's words before an iteration in which they are due (see
+// barrier_reached).
+__global__ __launch_bounds__(256) void k_barrier_clear(Dev D, uint32_t it) {
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (e < D.nbflags) D.bflags[e] = barrier_epoch(it, 0);
 }
 
 // Buffer 1 of the double-buffered synchronous schedules from buffer 0 (dir 0),
@@ -3215,7 +3216,7 @@ __global__ __launch_bounds__(1024) void k_construct_sync_spm(Dev D, Iter A) {
       if (active && lane < 2)
         lead = spm_register(D, 2 * ant + lane, lane == 0 ? cur : next, lane == 0 ? next : cur);
       const uint64_t leads = __ballot(lead);
-      grid_barrier_f(D, gbar, barrier_epoch(A, ++bar));
+      grid_barrier_f(D, gbar, barrier_epoch(A.it, ++bar));
       if (leads) {
         const int hv = __hip_atomic_load(D.upd_head + (lane == 0 ? cur : next), __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);
@@ -3228,7 +3229,7 @@ __global__ __launch_bounds__(1024) void k_construct_sync_spm(Dev D, Iter A) {
                          tn, hits, misses);
       }
       if (t < n) {
-        grid_barrier_f(D, gbar, barrier_epoch(A, ++bar));
+        grid_barrier_f(D, gbar, barrier_epoch(A.it, ++bar));
         if (!(leads & 2u)) pn = spm_record<true>(D, next, lane);
       }
     }
@@ -4538,6 +4539,11 @@ hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, 
     const bool odd = in_lds ? ((uint32_t)(d.n - 1) / it.lperiod) & 1 : d.n & 1;
     const int words = in_lds ? 4 * kSyncMaxAnts * grid : 0;
     const dim3 gb((unsigned)(((size_t)d.n * d.ldn + 255) / 256));
+    if (!in_lds && barrier_clear_due(it.it)) {
+      hipLaunchKernelGGL(k_barrier_clear, dim3((d.nbflags + 255) / 256), dim3(256), 0, s, d, it.it);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
     if (dbuf) {
       hipLaunchKernelGGL(k_sync_buf, gb, dim3(256), 0, s, d, 0, words);
       const hipError_t e = hipGetLastError();

@@ -37,4 +37,21 @@ ACS_PROTOCOL void queue_round(int *words, uint32_t round, int wave, int heads, S
   sync();
 }
 
+// Grid barrier of the synchronous kernels: a flag word says at which barrier its
+// writer has arrived, as an epoch: iteration << 17 | barrier, modulo 2^32 (a
+// construction has fewer than 2^17 - 1 barriers, from 1 on).
+constexpr int kBarrierBits = 17;
+ACS_PROTOCOL uint32_t barrier_epoch(uint32_t it, uint32_t bar) { return it << kBarrierBits | bar; }
+
+// Whether the flag's writer has arrived at the barrier of this epoch.  It can be
+// one barrier ahead of a block that still waits, never two: the second needs that
+// block's own arrival.  Anything else is what an earlier launch left.  Which words
+// a launch writes depends on where its blocks are placed, so a word may be any
+// number of launches old; only one exactly 32768 iterations old could be taken
+// for this epoch, and every kBarrierClear iterations all words are set to
+// barrier_epoch(it, 0), which no barrier from there to the next time is.
+constexpr uint32_t kBarrierClear = 1u << 14;
+ACS_PROTOCOL bool barrier_reached(uint32_t flag, uint32_t epoch) { return flag - epoch <= 1u; }
+ACS_PROTOCOL bool barrier_clear_due(uint32_t it) { return it % kBarrierClear == 0; }
+
 }  // namespace acs

@@ -63,10 +63,41 @@ void queue_rounds() {
     }
 }
 
+// No word that earlier launches left, of whatever age, passes for a barrier of
+// this one; a block at the barrier or one ahead does.
+void barrier_epochs() {
+  const uint32_t bars[] = {1, 2, 3, 1000, 70000, 131069};  // the last: two a step at the largest n
+  const uint32_t its[] = {0, 1, 5, 16383, 16384, 16385, 30000, 32767, 32768, 49152, 100000, 1u << 28,
+                          0xffffffffu};
+  auto expect = [](bool want, uint32_t flag, uint32_t it, uint32_t bar, const char *what) {
+    if (acs::barrier_reached(flag, acs::barrier_epoch(it, bar)) == want) return;
+    if (failures++ < 8)
+      std::printf("barrier %u of iteration %u: %s flag %u\n", bar, it, what, flag);
+  };
+  for (uint32_t it : its)
+    for (uint32_t bar : bars) {
+      expect(true, acs::barrier_epoch(it, bar), it, bar, "own");
+      expect(true, acs::barrier_epoch(it, bar + 1), it, bar, "next");
+      expect(false, acs::barrier_epoch(it, bar - 1), it, bar, "earlier");
+      expect(false, acs::barrier_epoch(it, 0), it, bar, "cleared");
+      for (uint32_t age = 1; age < 32768 && age <= it; ++age)
+        for (uint32_t left : bars) expect(false, acs::barrier_epoch(it - age, left), it, bar, "old");
+      // the words as the last clearing left them
+      uint32_t cleared = it;
+      while (!acs::barrier_clear_due(cleared)) --cleared;
+      expect(false, acs::barrier_epoch(cleared, 0), it, bar, "cleared earlier");
+      if (it - cleared >= 32768) {
+        std::printf("iteration %u: words uncleared for %u iterations\n", it, it - cleared);
+        ++failures;
+      }
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   if (argc == 2 && !std::strcmp(argv[1], "queue_round")) queue_rounds();
+  else if (argc == 2 && !std::strcmp(argv[1], "barrier")) barrier_epochs();
   else return 2;
   if (!failures) std::puts("ok");
   return failures ? 1 : 0;
