@@ -481,7 +481,7 @@ int init_handle(acs_t *h, const double *coords_xy, int32_t n, const acs_params *
   }
 
   if (p->mode == ACS_SYNC) {
-    const int cap = acs::max_sync_ants(d, (int)p->memory);
+    const int cap = acs::plan_sync(&d, (int)p->memory);
     if (m > cap)
       return fail(ACS_E_UNSUPPORTED, "m = %d ants exceed the %d one synchronous launch holds",
                   m, cap);

@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "acs_sync_shape.hpp"
+
 struct acs_params;
 
 namespace acs {
@@ -82,6 +84,8 @@ struct Dev {
   uint32_t *sync;          // [0] unused, [1] error flag
   uint32_t *bflags;            // synchronous mode: the grid barrier's words
   int32_t nbflags;             //   words in bflags
+  int32_t sync_apb;            //   ants per block
+  int32_t sync_lds;            //   1: the dense kernel with the pheromone in LDS
   uint32_t wait_limit;         // polls before a bounded wait gives up (0: the
                                //   kernels' own limits)
 };
@@ -131,44 +135,10 @@ hipError_t launch_fill(const Dev &d, float tau0, uint32_t dmax, bool eta_falls, 
 hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, int lanes,
                             int queued, hipStream_t s, hipEvent_t ev0 = nullptr,
                             hipEvent_t ev1 = nullptr);
-// Ants per block of the synchronous kernels.  Every phase of a step lasts as
-// long as its slowest ant, and the waves of a SIMD run it in lockstep, so the
-// ants are spread over all compute units (256), at most kSyncMaxAnts per
-// block.
-constexpr int kSyncMaxAnts = 16, kSyncBlocks = 256;
-inline int sync_ants_per_block(int m) {
-  const int a = (m + kSyncBlocks - 1) / kSyncBlocks;
-  return a < kSyncMaxAnts ? a : kSyncMaxAnts;
-}
-inline int sync_blocks(int m) {
-  return (m + sync_ants_per_block(m) - 1) / sync_ants_per_block(m);
-}
-// Dense synchronous construction with the candidate entries' pheromone in
-// every block's LDS (k_construct_sync_lds).  Its ants per block: about 32
-// blocks, up to 64 as long as they hold the ants, at least 4 each; a block then
-// has a thread for every ant of the colony.
-inline int sync_lds_ants_per_block(int m) {
-  const int a = m <= 512 ? (m + 31) / 32 : (m + 63) / 64;
-  return a < 4 ? 4 : a;
-}
-// It is taken where 64 blocks hold the ants, n * cl floats and 16 ants' bitmaps
-// fit a block's LDS, and the blocks' words (two sets of 128 bytes each) fit the
-// place of ctau, which it does not use.
-constexpr size_t kSyncLdsBytes = 156 * 1024;
-inline bool sync_lds(int n, int m, int cl) {
-  const int a = sync_lds_ants_per_block(m);
-  return m <= 64 * kSyncMaxAnts &&
-         (size_t)n * cl * 4 + (size_t)kSyncMaxAnts * ((n + 31) / 32) * 4 <= kSyncLdsBytes &&
-         (size_t)((m + a - 1) / a) * 256 <= (size_t)n * cl * 4;
-}
-// Words of the grid barrier: the XCDs' lists and mailboxes, a word per block.
-constexpr int kXcds = 8;
-inline size_t sync_barrier_words(int m) {
-  const size_t g = (size_t)sync_blocks(m);
-  return kXcds * (((g + 31) & ~(size_t)31) + 32) + g;
-}
-// Largest m a synchronous launch can keep resident for this instance.
-int max_sync_ants(const Dev &d, int memory);
+// Chooses the launch shape of the synchronous construction on this device
+// (d.sync_apb, d.sync_lds) and returns the largest m that one launch can keep
+// resident for this instance.
+int plan_sync(Dev *d, int memory);
 // The iteration's end: best tours, the candidates' pheromone back in the
 // records where the construction kept it apart, global update.  mode, memory,
 // lanes and queued as given to launch_construct.

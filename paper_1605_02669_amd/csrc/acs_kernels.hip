@@ -4385,8 +4385,6 @@ size_t lds_bytes(const Dev &D, int block) {
   return (size_t)(block / 64) * D.vw * sizeof(uint32_t);
 }
 
-constexpr int kSyncBlock = 1024;
-static_assert(kSyncBlock == 64 * kSyncMaxAnts, "the largest synchronous block");
 constexpr int kAsyncBlock = 256;
 
 }  // namespace
@@ -4481,7 +4479,7 @@ static hipError_t queued_ants_per_block(int m, bool counted, int *na) {
 // The selective memory's common shapes get kernels with s = 8 and the
 // candidate lanes fixed (the trail lookup unrolls).
 static const void *sync_kernel(const Dev &d, int memory) {
-  if (memory == 0 && sync_lds(d.n, d.m, d.cl))
+  if (d.sync_lds)
     return d.cl <= 32 ? reinterpret_cast<const void *>(&k_construct_sync_lds<true>)
                       : reinterpret_cast<const void *>(&k_construct_sync_lds<false>);
   if (memory == 0) return reinterpret_cast<const void *>(&k_construct_sync_dense);
@@ -4489,6 +4487,11 @@ static const void *sync_kernel(const Dev &d, int memory) {
   if (d.cl <= 16) return reinterpret_cast<const void *>(&k_construct_sync_spm<8, 16>);
   if (d.cl <= 32) return reinterpret_cast<const void *>(&k_construct_sync_spm<8, 32>);
   return reinterpret_cast<const void *>(&k_construct_sync_spm<8, 64>);
+}
+
+// Dynamic LDS of a block of `ants` ants of that kernel.
+static size_t sync_lds_size(const Dev &d, int ants) {
+  return (d.sync_lds ? (size_t)d.n * d.cl * sizeof(float) : 0) + lds_bytes(d, 64 * ants);
 }
 
 // Whether the construction keeps the candidates' pheromone in ctau.
@@ -4527,8 +4530,8 @@ hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, 
     return e != hipSuccess ? e : mark(ev1);
   }
   if (mode == 0) {
-    const bool in_lds = memory == 0 && sync_lds(d.n, d.m, d.cl);
-    const int apb = in_lds ? sync_lds_ants_per_block(d.m) : sync_ants_per_block(d.m);
+    const bool in_lds = d.sync_lds != 0;
+    const int apb = d.sync_apb;
     const int grid = (d.m + apb - 1) / apb;
     Dev dd = d;
     Iter a = it;
@@ -4552,8 +4555,7 @@ hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, 
     const hipError_t me = mark(ev0);
     if (me != hipSuccess) return me;
     hipError_t e = hipLaunchCooperativeKernel(fn, dim3(grid), dim3(64 * apb), args,
-                                              (in_lds ? (size_t)d.n * d.cl * sizeof(float) : 0) +
-                                                  lds_bytes(d, 64 * apb), s);
+                                              sync_lds_size(d, apb), s);
     if (e == hipSuccess) e = mark(ev1);
     if (e != hipSuccess || !dbuf || !odd) return e;
     hipLaunchKernelGGL(k_sync_buf, gb, dim3(256), 0, s, d, 1, words);
@@ -4657,17 +4659,28 @@ hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, 
   return e != hipSuccess ? e : mark(ev1);
 }
 
-int max_sync_ants(const Dev &d, int memory) {
-  int per_cu = 0;
-  const void *fn = sync_kernel(d, memory);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kSyncBlock,
-                                                   lds_bytes(d, kSyncBlock)) != hipSuccess)
-    return 0;
+int plan_sync(Dev *d, int memory) {
   int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 0;
-  return per_cu * cus * (kSyncBlock / 64);
+  // blocks of `ants` ants of the kernel chosen by d->sync_lds on the device at once
+  auto resident = [&](int ants) {
+    int per_cu = 0;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &per_cu, sync_kernel(*d, memory), 64 * ants, sync_lds_size(*d, ants));
+    if (e == hipSuccess) return per_cu * cus;
+    (void)hipGetLastError();  // not the last error of the launches that follow
+    return 0;
+  };
+  if (memory == 0 && sync_lds(d->n, d->m, d->cl)) {
+    d->sync_lds = 1;
+    d->sync_apb = sync_lds_ants_per_block(d->m);
+    if (sync_lds_taken(d->n, d->m, d->cl, resident(d->sync_apb))) return 64 * kSyncMaxAnts;
+    d->sync_lds = 0;
+  }
+  d->sync_apb = sync_ants_per_block_on(d->m, resident(sync_ants_per_block(d->m)));
+  return resident(kSyncMaxAnts) * kSyncMaxAnts;
 }
 
 hipError_t launch_local_search(const Dev &d, int kind, hipStream_t s) {

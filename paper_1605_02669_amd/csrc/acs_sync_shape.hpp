@@ -1,0 +1,62 @@
+// Launch shapes of the synchronous constructions: which kernel, how many ants a
+// block, the words of the grid barrier.  Host arithmetic without the GPU.
+#pragma once
+#include <stddef.h>
+#include <stdint.h>
+
+namespace acs {
+
+// Ants per block of the synchronous kernels.  Every phase of a step lasts as
+// long as its slowest ant, and the waves of a SIMD run it in lockstep, so the
+// ants are spread over all compute units (256), at most kSyncMaxAnts per
+// block.
+constexpr int kSyncMaxAnts = 16, kSyncBlocks = 256;
+inline int sync_ants_per_block(int m) {
+  const int a = (m + kSyncBlocks - 1) / kSyncBlocks;
+  return a < kSyncMaxAnts ? a : kSyncMaxAnts;
+}
+inline int sync_blocks(int m) {
+  return (m + sync_ants_per_block(m) - 1) / sync_ants_per_block(m);
+}
+// Dense synchronous construction with the candidate entries' pheromone in
+// every block's LDS (k_construct_sync_lds).  Its ants per block: about 32
+// blocks, up to 64 as long as they hold the ants, at least 4 each; a block then
+// has a thread for every ant of the colony.
+inline int sync_lds_ants_per_block(int m) {
+  const int a = m <= 512 ? (m + 31) / 32 : (m + 63) / 64;
+  return a < 4 ? 4 : a;
+}
+// It can be taken where 64 blocks hold the ants, n * cl floats and 16 ants' bitmaps
+// fit a block's LDS, and the blocks' words (two sets of 128 bytes each) fit the
+// place of ctau, which it does not use.
+constexpr size_t kSyncLdsBytes = 156 * 1024;
+inline bool sync_lds(int n, int m, int cl) {
+  const int a = sync_lds_ants_per_block(m);
+  return m <= 64 * kSyncMaxAnts &&
+         (size_t)n * cl * 4 + (size_t)kSyncMaxAnts * ((n + 31) / 32) * 4 <= kSyncLdsBytes &&
+         (size_t)((m + a - 1) / a) * 256 <= (size_t)n * cl * 4;
+}
+// It is taken where its blocks also fit the device at once: all blocks of a
+// synchronous kernel wait for each other, so all have to be resident.  `resident`:
+// blocks the device holds, with this kernel's block size and all of its LDS.  (256
+// compute units always hold 64 such blocks; a partition of the card may not, and
+// then the kernel below takes the colony.)
+inline int sync_lds_blocks(int m) {
+  return (m + sync_lds_ants_per_block(m) - 1) / sync_lds_ants_per_block(m);
+}
+inline bool sync_lds_taken(int n, int m, int cl, int resident) {
+  return sync_lds(n, m, cl) && sync_lds_blocks(m) <= resident;
+}
+// Ants per block of the other kernels on a device that holds `resident` blocks of
+// sync_ants_per_block(m): fuller blocks where it does not hold all of those.
+inline int sync_ants_per_block_on(int m, int resident) {
+  return sync_blocks(m) <= resident ? sync_ants_per_block(m) : kSyncMaxAnts;
+}
+// Words of the grid barrier: the XCDs' lists and mailboxes, a word per block.
+constexpr int kXcds = 8;
+inline size_t sync_barrier_words(int m) {
+  const size_t g = (size_t)sync_blocks(m);
+  return kXcds * (((g + 31) & ~(size_t)31) + 32) + g;
+}
+
+}  // namespace acs

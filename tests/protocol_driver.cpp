@@ -1,5 +1,6 @@
 // The kernels' shared-word protocols (csrc/acs_protocol.hpp) on host threads,
-// one for each wave, with one of them held back at a time.
+// one for each wave, with one of them held back at a time, and the launch shapes
+// of the synchronous kernels (csrc/acs_sync_shape.hpp).
 #include <pthread.h>
 #include <unistd.h>
 
@@ -9,6 +10,7 @@
 #include <vector>
 
 #include "acs_protocol.hpp"
+#include "acs_sync_shape.hpp"
 
 namespace {
 
@@ -93,11 +95,40 @@ void barrier_epochs() {
     }
 }
 
+// Every block of a synchronous launch is resident on the device, whatever share
+// of the card it is.
+void sync_residency() {
+  auto expect = [](bool ok, int n, int m, int cl, int resident, const char *what) {
+    if (ok) return;
+    std::printf("n %d, m %d, cl %d, %d blocks resident: %s\n", n, m, cl, resident, what);
+    ++failures;
+  };
+  const int ns[] = {30, 198, 1000, 2392, 20000}, cls[] = {1, 12, 16, 32, 64};
+  for (int n : ns)
+    for (int cl : cls)
+      for (int m = 1; m <= 4096; m += m < 1100 ? 1 : 97)
+        for (int resident : {0, 16, 31, 32, 33, 63, 64, 256}) {
+          if (acs::sync_lds_taken(n, m, cl, resident))
+            expect(acs::sync_lds_blocks(m) <= resident, n, m, cl, resident,
+                   "pheromone in LDS, but not all blocks fit");
+          if (resident >= 64)
+            expect(acs::sync_lds_taken(n, m, cl, resident) == acs::sync_lds(n, m, cl), n, m, cl,
+                   resident, "another kernel than on the whole card");
+          const int a = acs::sync_ants_per_block_on(m, resident);
+          expect((m + a - 1) / a <= resident || a == acs::kSyncMaxAnts, n, m, cl, resident,
+                 "more blocks than fit");
+          if (resident >= 256)
+            expect(a == acs::sync_ants_per_block(m), n, m, cl, resident,
+                   "another block size than on the whole card");
+        }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   if (argc == 2 && !std::strcmp(argv[1], "queue_round")) queue_rounds();
   else if (argc == 2 && !std::strcmp(argv[1], "barrier")) barrier_epochs();
+  else if (argc == 2 && !std::strcmp(argv[1], "sync_residency")) sync_residency();
   else return 2;
   if (!failures) std::puts("ok");
   return failures ? 1 : 0;

@@ -1,7 +1,8 @@
 """The protocols by which the kernels' waves and blocks share words
 (csrc/acs_protocol.hpp), run on the CPU from the header that the kernels
 include: the result may not depend on which wave is late, nor on what earlier
-launches left in the words."""
+launches left in the words, and all blocks of a launch whose blocks wait for each
+other have to be resident."""
 import os
 import shutil
 import subprocess
@@ -25,7 +26,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("name", ["queue_round", "barrier"])
+@pytest.mark.parametrize("name", ["queue_round", "barrier", "sync_residency"])
 def test_protocol(driver, name):
     r = subprocess.run([driver, name], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
