@@ -123,7 +123,7 @@ Layout make_layout(int n, int m, int cl, int ldn, int memory, int s, int mode) {
     // lists where they need more (up to 1200 ants), a larger region where
     // that is too small as well
     const size_t words = sizeof(uint32_t) * acs::sync_barrier_words(m);
-    const size_t lines = 128 * (size_t)((m + 15) / 16 + 1);
+    const size_t lines = 128 * (size_t)(((int64_t)m + 15) / 16 + 1);
     const bool in_cand =
         words > lines && memory == ACS_DENSE && words <= sizeof(int32_t) * (size_t)n * cl;
     L.bflags = take(in_cand ? lines : std::max(lines, words));

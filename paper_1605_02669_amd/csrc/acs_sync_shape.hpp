@@ -9,21 +9,22 @@ namespace acs {
 // Ants per block of the synchronous kernels.  Every phase of a step lasts as
 // long as its slowest ant, and the waves of a SIMD run it in lockstep, so the
 // ants are spread over all compute units (256), at most kSyncMaxAnts per
-// block.
+// block.  (m is a caller's word and may be any int here: a workspace's size is asked
+// before it is checked.)
 constexpr int kSyncMaxAnts = 16, kSyncBlocks = 256;
 inline int sync_ants_per_block(int m) {
-  const int a = (m + kSyncBlocks - 1) / kSyncBlocks;
-  return a < kSyncMaxAnts ? a : kSyncMaxAnts;
+  const int64_t a = ((int64_t)m + kSyncBlocks - 1) / kSyncBlocks;
+  return a < 1 ? 1 : a < kSyncMaxAnts ? (int)a : kSyncMaxAnts;
 }
 inline int sync_blocks(int m) {
-  return (m + sync_ants_per_block(m) - 1) / sync_ants_per_block(m);
+  return (int)(((int64_t)m + sync_ants_per_block(m) - 1) / sync_ants_per_block(m));
 }
 // Dense synchronous construction with the candidate entries' pheromone in
 // every block's LDS (k_construct_sync_lds).  Its ants per block: about 32
 // blocks, up to 64 as long as they hold the ants, at least 4 each; a block then
 // has a thread for every ant of the colony.
 inline int sync_lds_ants_per_block(int m) {
-  const int a = m <= 512 ? (m + 31) / 32 : (m + 63) / 64;
+  const int a = m <= 512 ? (m + 31) / 32 : m <= 64 * kSyncMaxAnts ? (m + 63) / 64 : kSyncMaxAnts;
   return a < 4 ? 4 : a;
 }
 // It can be taken where 64 blocks hold the ants, n * cl floats and 16 ants' bitmaps
@@ -32,7 +33,7 @@ inline int sync_lds_ants_per_block(int m) {
 constexpr size_t kSyncLdsBytes = 156 * 1024;
 inline bool sync_lds(int n, int m, int cl) {
   const int a = sync_lds_ants_per_block(m);
-  return m <= 64 * kSyncMaxAnts &&
+  return m >= 1 && m <= 64 * kSyncMaxAnts &&
          (size_t)n * cl * 4 + (size_t)kSyncMaxAnts * ((n + 31) / 32) * 4 <= kSyncLdsBytes &&
          (size_t)((m + a - 1) / a) * 256 <= (size_t)n * cl * 4;
 }
@@ -42,7 +43,7 @@ inline bool sync_lds(int n, int m, int cl) {
 // compute units always hold 64 such blocks; a partition of the card may not, and
 // then the kernel below takes the colony.)
 inline int sync_lds_blocks(int m) {
-  return (m + sync_lds_ants_per_block(m) - 1) / sync_lds_ants_per_block(m);
+  return (int)(((int64_t)m + sync_lds_ants_per_block(m) - 1) / sync_lds_ants_per_block(m));
 }
 inline bool sync_lds_taken(int n, int m, int cl, int resident) {
   return sync_lds(n, m, cl) && sync_lds_blocks(m) <= resident;
