@@ -1635,12 +1635,10 @@ __global__ __launch_bounds__(256) void k_sync_buf(Dev D, int dir, int words) {
 // unit's issue slots bound the first round, the barriers and single choices the
 // others.  Rounds of 16 ants, each with its own draws, global reads of the
 // current cities and conflict search, took 11.1 us a step at m = 64 and 461 us
-// at m = n = 2392; this takes 5.5 and 223.  Groups of 64 take 6.1 and 248,
-// groups of 256 choose more often in vain (n = 500, m = 256: 46 us a step
-// against 34; 45 before).
+// at m = n = 2392; this takes 5.5 and 223.  How many ants make a group
+// (`group`, at most kSeqGroup) depends on how often they meet: see seq_group.
 // ---------------------------------------------------------------------------
-constexpr int kSeqWaves = 16;
-constexpr int kSeqGroup = 128;   // ants choosing at once
+constexpr int kSeqWaves = 16;    // a group is a multiple of it
 constexpr int kSeqSlots = kSeqGroup / kSeqWaves;  // per wave
 constexpr int kSeqRows = 4096;   // slots of the table of rows (power of two)
 constexpr int kSeqCur = 4096;    // current cities in LDS for up to so many ants
@@ -1659,7 +1657,8 @@ __device__ __forceinline__ uint32_t pack_choice(int next, int k, int kr, bool ro
 // the same value (every map is applied to both), so a committing ant stores
 // the map of the value it read to both without reading the second.
 template <bool VIS_LDS>
-__global__ __launch_bounds__(64 * kSeqWaves) void k_construct_seq_dense(Dev D, Iter A) {
+__global__ __launch_bounds__(64 * kSeqWaves) void k_construct_seq_dense(Dev D, Iter A,
+                                                                        int group) {
   extern __shared__ uint32_t smem[];
   __shared__ uint32_t s_rows[kSeqRows];   // round (counted down) << 8 | least ant
   __shared__ uint32_t s_choice[kSeqGroup];
@@ -1695,17 +1694,17 @@ __global__ __launch_bounds__(64 * kSeqWaves) void k_construct_seq_dense(Dev D, I
   for (int t = 1; t < n; ++t) {
     const bool upd = --left == 0;
     if (upd) left = A.lperiod;
-    for (int base = 0; base < m; base += kSeqGroup) {
-      const int g = min(kSeqGroup, m - base);
+    for (int base = 0; base < m; base += group) {
+      const int g = min(group, m - base);
       // draws of this wave's ants: lane l holds ant slot l % kSeqSlots at step
       // (t & ~3) + l / kSeqSlots
-      if (m > kSeqGroup || (t & 3) == 0 || t == 1)
+      if (m > group || (t & 3) == 0 || t == 1)
         draws = philox10(make_uint4((uint32_t)((t & ~3) + lane / kSeqSlots),
                                     (uint32_t)(base + lane % kSeqSlots * kSeqWaves + wv), A.it,
                                     A.instance),
                          A.key0, A.key1);
       // (one group: its cities are kept up to date where its ants commit)
-      if (t == 1 || m > kSeqGroup) {
+      if (t == 1 || m > group) {
         if (tid < g) {
           s_now[tid] =
               near ? s_cur[base + tid] : (uint16_t)D.tours[(size_t)(base + tid) * n + t - 1];
@@ -4522,14 +4521,15 @@ hipError_t launch_construct(const Dev &d, const Iter &it, int mode, int memory, 
   }
   if (mode == 3) {
     const size_t words = (size_t)d.m * ((d.n + 31) / 32);
+    const int group = seq_group(d.n, it.lperiod);
     const hipError_t me = mark(ev0);
     if (me != hipSuccess) return me;
     if (words <= (size_t)kSeqLdsWords)
       hipLaunchKernelGGL(k_construct_seq_dense<true>, dim3(1), dim3(64 * kSeqWaves),
-                         words * sizeof(uint32_t), s, d, it);
+                         words * sizeof(uint32_t), s, d, it, group);
     else
       hipLaunchKernelGGL(k_construct_seq_dense<false>, dim3(1), dim3(64 * kSeqWaves), 0, s, d,
-                         it);
+                         it, group);
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : mark(ev1);
   }

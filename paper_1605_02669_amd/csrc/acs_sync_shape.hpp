@@ -1,5 +1,6 @@
-// Launch shapes of the synchronous constructions: which kernel, how many ants a
-// block, the words of the grid barrier.  Host arithmetic without the GPU.
+// Launch shapes of the synchronous and sequential constructions: which kernel, how
+// many ants a block or a group, the words of the grid barrier.  Host arithmetic
+// without the GPU.
 #pragma once
 #include <stddef.h>
 #include <stdint.h>
@@ -58,6 +59,25 @@ constexpr int kXcds = 8;
 inline size_t sync_barrier_words(int m) {
   const size_t g = (size_t)sync_blocks(m);
   return kXcds * (((g + 31) & ~(size_t)31) + 32) + g;
+}
+
+// Ants that choose at once in the sequential construction: a multiple of 16, at
+// most kSeqGroup.  A round commits the ants before the first whose row an earlier
+// one writes, so the fewer cities there are, and the more often steps update, the
+// more of a large group's choices are made again.  Best group by measurement (ms
+// per iteration with it, with 128, and with the former kernel's rounds of 16 ants;
+// cl = 32), update period 1:
+//   n = 10, m = 200     16   1.35   2.98   1.69      n = 200, m = 1000    32   35.8   46.4   43.6
+//   n = 50, m = 1000    24   15.5   28.1   18.9      n = 300, m = 1000    64   44.6   51.3   57.0
+//   n = 100, m = 1000   24   23.9   36.9   28.2      n = 500, m = 500     64   30.6   32.9   43.9
+//   n = 150, m = 1000   32   31.3   43.8   36.9      n = 1000, m = 1000   96  110.9  111.6  162.6
+// and period 2: n = 50 24 (9.55, 14.9, 12.3), n = 100 32 (15.5, 20.2, 20.7), n = 200
+// 64 (23.9, 27.0, 34.5), n = 500 96 (21.4, 21.7, 38.1); at period 16 128 from n = 100
+// on.  The line through these is 16 + n * period / 10.
+constexpr int kSeqGroup = 128;
+inline int seq_group(int n, uint32_t period) {
+  const uint64_t g = 16 + (uint64_t)n * period / 10;
+  return g >= kSeqGroup ? kSeqGroup : (int)(g + 8) & ~15;
 }
 
 }  // namespace acs

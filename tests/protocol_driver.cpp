@@ -1,6 +1,6 @@
 // The kernels' shared-word protocols (csrc/acs_protocol.hpp) on host threads,
 // one for each wave, with one of them held back at a time, and the launch shapes
-// of the synchronous kernels (csrc/acs_sync_shape.hpp).
+// of the synchronous and sequential kernels (csrc/acs_sync_shape.hpp).
 #include <pthread.h>
 #include <unistd.h>
 
@@ -123,12 +123,37 @@ void sync_residency() {
         }
 }
 
+// The sequential construction's groups: whole waves' worth, small where ants meet
+// often, the largest where they rarely do.
+void seq_groups() {
+  auto expect = [](bool ok, int n, uint32_t period, int g) {
+    if (ok) return;
+    std::printf("seq_group(%d, %u) = %d\n", n, period, g);
+    ++failures;
+  };
+  const uint32_t periods[] = {1, 2, 3, 16, 250, 65536, 0x7fffffffu, 0xffffffffu};
+  for (uint32_t p : periods)
+    for (int n = 3, last = 16; n <= 65535; ++n) {
+      const int g = acs::seq_group(n, p);
+      expect(g >= last && g % 16 == 0 && g <= acs::kSeqGroup, n, p, g);
+      last = g;
+    }
+  // where the largest group was slower than rounds of 16 ants
+  for (int n : {10, 30, 50}) expect(acs::seq_group(n, 1) == 16, n, 1, acs::seq_group(n, 1));
+  for (int n : {100, 150, 200}) expect(acs::seq_group(n, 1) == 32, n, 1, acs::seq_group(n, 1));
+  expect(acs::seq_group(50, 2) <= 32, 50, 2, acs::seq_group(50, 2));
+  // where it is the fastest
+  for (int n : {1200, 2392, 8000}) expect(acs::seq_group(n, 1) == 128, n, 1, acs::seq_group(n, 1));
+  expect(acs::seq_group(100, 16) == 128, 100, 16, acs::seq_group(100, 16));
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   if (argc == 2 && !std::strcmp(argv[1], "queue_round")) queue_rounds();
   else if (argc == 2 && !std::strcmp(argv[1], "barrier")) barrier_epochs();
   else if (argc == 2 && !std::strcmp(argv[1], "sync_residency")) sync_residency();
+  else if (argc == 2 && !std::strcmp(argv[1], "seq_groups")) seq_groups();
   else return 2;
   if (!failures) std::puts("ok");
   return failures ? 1 : 0;

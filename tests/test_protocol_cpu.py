@@ -26,7 +26,8 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("name", ["queue_round", "barrier", "sync_residency"])
+@pytest.mark.parametrize("name", ["queue_round", "barrier", "sync_residency",
+                                  "seq_groups"])
 def test_protocol(driver, name):
     r = subprocess.run([driver, name], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
