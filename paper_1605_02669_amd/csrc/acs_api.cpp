@@ -703,10 +703,21 @@ int acs_candidates(acs_t *h, int32_t *out, size_t count) {
     HIP_TRY(hipMemcpy(out, h->ws + h->L.cand, need * sizeof(int32_t), hipMemcpyDeviceToHost));
     return ACS_OK;
   }
-  std::vector<uint32_t> rec(4 * need);  // dense memory: first word of each record
-  HIP_TRY(hipMemcpy(rec.data(), h->ws + h->L.crec, rec.size() * sizeof(uint32_t),
-                    hipMemcpyDeviceToHost));
-  for (size_t e = 0; e < need; ++e) out[e] = (int32_t)rec[4 * e];
+  // dense memory: the first words of the records.  They are read through the
+  // caller's buffer, whose rest holds a quarter as many records as ints, so that the
+  // call takes no host memory of its own (and has none to run out of).
+  const char *const recs = h->ws + h->L.crec;
+  constexpr size_t kLast = 4096;
+  uint32_t last[4 * kLast];
+  size_t e = 0;
+  while (need - e > kLast) {
+    const size_t q = (need - e) / 4;
+    HIP_TRY(hipMemcpy(out + e, recs + 16 * e, 16 * q, hipMemcpyDeviceToHost));
+    for (size_t i = 0; i < q; ++i) out[e + i] = out[e + 4 * i];
+    e += q;
+  }
+  HIP_TRY(hipMemcpy(last, recs + 16 * e, 16 * (need - e), hipMemcpyDeviceToHost));
+  for (size_t i = 0; e < need; ++i, ++e) out[e] = (int32_t)last[4 * i];
   return ACS_OK;
 }
 
