@@ -698,26 +698,16 @@ int acs_candidates(acs_t *h, int32_t *out, size_t count) {
   if (!live(h)) return fail(ACS_E_STATE, "invalid handle");
   const size_t need = (size_t)h->n * h->cl;
   if (!out || count < need) return fail(ACS_E_BUFSIZE, "need %zu ints", need);
+  // the lists where they were built, unless something else has taken the place
+  // (see make_layout); the records' first words then, gathered on the device, since
+  // the records are four times as long, in ctau, which holds nothing between calls
+  size_t at = h->L.cand;
+  if (h->L.ccnt == at || h->L.bflags == at) {
+    at = h->L.ctau;
+    HIP_TRY(acs::launch_cand_out(h->dev, reinterpret_cast<int32_t *>(h->ws + at), h->stream));
+  }
   HIP_TRY(hipStreamSynchronize(h->stream));
-  if (h->p.memory == ACS_SPM) {
-    HIP_TRY(hipMemcpy(out, h->ws + h->L.cand, need * sizeof(int32_t), hipMemcpyDeviceToHost));
-    return ACS_OK;
-  }
-  // dense memory: the first words of the records.  They are read through the
-  // caller's buffer, whose rest holds a quarter as many records as ints, so that the
-  // call takes no host memory of its own (and has none to run out of).
-  const char *const recs = h->ws + h->L.crec;
-  constexpr size_t kLast = 4096;
-  uint32_t last[4 * kLast];
-  size_t e = 0;
-  while (need - e > kLast) {
-    const size_t q = (need - e) / 4;
-    HIP_TRY(hipMemcpy(out + e, recs + 16 * e, 16 * q, hipMemcpyDeviceToHost));
-    for (size_t i = 0; i < q; ++i) out[e + i] = out[e + 4 * i];
-    e += q;
-  }
-  HIP_TRY(hipMemcpy(last, recs + 16 * e, 16 * (need - e), hipMemcpyDeviceToHost));
-  for (size_t i = 0; e < need; ++i, ++e) out[e] = (int32_t)last[4 * i];
+  HIP_TRY(hipMemcpy(out, h->ws + at, need * sizeof(int32_t), hipMemcpyDeviceToHost));
   return ACS_OK;
 }
 

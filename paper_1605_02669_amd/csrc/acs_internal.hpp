@@ -118,6 +118,8 @@ hipError_t launch_nn_tour(const Dev &d, const int32_t *cand_tmp, uint16_t *near,
 // starts, then the cities in cell order; cnt: gnx * gny ints of scratch.
 hipError_t launch_grid(const Dev &d, int32_t *cnt, hipStream_t s);
 hipError_t launch_crec(const Dev &d, const int32_t *cand_tmp, float tau0, hipStream_t s);
+// The candidate lists (n x cl) from the records.
+hipError_t launch_cand_out(const Dev &d, int32_t *out, hipStream_t s);
 // Initial pheromone, eta^beta of every entry and of the prefix, counters and
 // state.  eta_falls: the table never grows with the distance (up to dmax).
 hipError_t launch_fill(const Dev &d, float tau0, uint32_t dmax, bool eta_falls, hipStream_t s);

@@ -824,6 +824,11 @@ __global__ __launch_bounds__(256) void k_crec(Dev D, const int32_t *cand, float 
   const_cast<int8_t *>(D.rpos)[e] = (int8_t)r;
 }
 
+__global__ __launch_bounds__(256) void k_cand_out(Dev D, int32_t *out) {
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (e < D.n * D.cl) out[e] = (int32_t)D.crec[e].x;
+}
+
 // A construction with an updater wave keeps the candidate entries' live
 // pheromone in ctau (a record's 32 values in one 128-byte line), so the
 // records the ants load are not written while it runs.  Before it, ctau
@@ -4452,6 +4457,11 @@ hipError_t launch_nn_tour(const Dev &d, const int32_t *cand_tmp, uint16_t *near,
 hipError_t launch_crec(const Dev &d, const int32_t *cand_tmp, float tau0, hipStream_t s) {
   const int total = d.n * d.cl;
   hipLaunchKernelGGL(k_crec, dim3((total + 255) / 256), dim3(256), 0, s, d, cand_tmp, tau0);
+  return hipGetLastError();
+}
+
+hipError_t launch_cand_out(const Dev &d, int32_t *out, hipStream_t s) {
+  hipLaunchKernelGGL(k_cand_out, dim3((d.n * d.cl + 255) / 256), dim3(256), 0, s, d, out);
   return hipGetLastError();
 }
 

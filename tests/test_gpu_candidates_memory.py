@@ -58,3 +58,26 @@ def test_lists(acs, n, cl):
     assert np.array_equal(col.cand(), orc.cand())
     col.close()
     orc.close()
+
+
+# wherever the lists' place holds something else after creation (updates' counts,
+# the grid barrier's words): the lists between iterations, and iterations as if
+# they had not been read
+@pytest.mark.parametrize("mode,memory,m,period", [
+    (0, 0, 200, 1), (0, 0, 200, 3), (0, 0, 1100, 1), (0, 0, 1100, 4), (0, 1, 40, 1), (1, 0, 1, 1),
+    (1, 0, 1, 5), (2, 0, 1, 1), (1, 1, 1, 1), (3, 0, 20, 1)])
+def test_lists_between_iterations(acs, mode, memory, m, period):
+    xy = inputs.uniform(300)
+    kw = dict(m=m, cl=24, mode=mode, memory=memory, seed=4, local_update_period=period)
+    read, left = acs.Colony(xy, **kw), acs.Colony(xy, **kw)
+    orc = oracle.Oracle(xy, m=1, cl=24)
+    for _ in range(3):
+        assert np.array_equal(read.cand(), orc.cand())
+        read.iterate(1)
+        left.iterate(1)
+        assert np.array_equal(read.tours(), left.tours())
+        if memory == 0:
+            assert np.array_equal(read.tau(), left.tau())
+    assert np.array_equal(read.cand(), orc.cand())
+    for c in (read, left, orc):
+        c.close()
