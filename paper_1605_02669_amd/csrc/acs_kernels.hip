@@ -89,16 +89,6 @@ __device__ __forceinline__ T wave_min(T v) {
   return v;
 }
 
-template <typename T>
-__device__ __forceinline__ T wave_max(T v) {
-#pragma unroll
-  for (int off = 32; off; off >>= 1) {
-    const T o = __shfl_xor(v, off, 64);
-    v = o > v ? o : v;
-  }
-  return v;
-}
-
 // Wave-wide unsigned max / min, all lanes active: quad and row permutations
 // by DPP, then the row-pair and half-wave swaps of gfx950.  Returns the
 // result as a wave-uniform value.
