@@ -361,7 +361,9 @@ int build(acs_t *h, const double *xy, float *eta_host) {
   b.b_loc = (float)(p.phi * (double)h->tau0);
   b.a_glob = (float)(1.0 - p.rho);
   b.tau0 = h->tau0;
-  b.lperiod = p.local_update_period;
+  // a tour has fewer than 2^16 steps: from there on every period means no update but
+  // the closing edge's, and a kernel may take it as a signed integer
+  b.lperiod = std::min(p.local_update_period, (uint32_t)INT32_MAX);
   b.rho = p.rho;
   return ACS_OK;
 }

@@ -2317,7 +2317,7 @@ __device__ __forceinline__ void ant_queued(const Dev &D, const Iter &A, int ant,
     const int lt = lane + t0;
     // bit t - t0 of `upd`: step t has a local update (after every
     // lperiod-th selected edge); of `greedy`: step t takes Eq. 1's argmax
-    const uint64_t upd = __builtin_amdgcn_ballot_w64((uint32_t)lt % A.lperiod == 0);
+    const uint64_t upd = __builtin_amdgcn_ballot_w64(lt % (int)A.lperiod == 0);
     const uint64_t greedy = __builtin_amdgcn_ballot_w64((draws.x >> 8) < A.q0_24);
     // lane t - t0 holds step t's crossing (x = kNoEntry: no update) and
     // tour entry; every crossing is a candidate move (kr = -2) unless the
