@@ -173,9 +173,9 @@ __device__ __forceinline__ float4 load_x(const float *X, int row, int rows) {
 // registers and takes two 16-row tiles per pass.  Bound by instruction issue:
 // a pass is 28 matrix instructions (24 us of them at 4.2 M rows) beside about
 // 100 vector ones, most of them the packing and the maxima between layers.
-// 4.2 M rows take 61 us (72 with a maximum per float, branches around the
-// loads, two stores a pass and 1024 blocks), 1000 rows 3.2 us (4.5 with the
-// 16 loads of W1 one after the other).
+// 4.2 M rows take 50.5 us a launch (63.5 with a maximum per float, branches around
+// the loads, two stores a pass and 1024 blocks), 1000 rows 3.4 us (4.3 with the 16
+// loads of W1 one after the other).
 constexpr int kFwdWaves = 4;
 
 __global__ __launch_bounds__(64 * kFwdWaves) void k_prior_forward(const float *P, const float *X,
@@ -571,7 +571,8 @@ hipError_t launch_prior_forward(const float *P, const float *X, int rows, float 
   const int tiles = (rows + 31) / 32;
   int blocks = (tiles + kFwdWaves - 1) / kFwdWaves;
   // three blocks per CU are what the registers allow at once (156 a wave): with
-  // a fourth, 256 blocks run alone at the end (4.2 M rows 67.3 us, with three 63.8)
+  // a fourth, 256 blocks run alone at the end (4.2 M rows 52.5 us, with three 50.5;
+  // 262144 rows 8.3 and 7.5)
   blocks = blocks < 768 ? (blocks > 0 ? blocks : 1) : 768;
   hipLaunchKernelGGL(k_prior_forward, dim3(blocks), dim3(64 * kFwdWaves), 0, s, P, X, rows, Z);
   return hipGetLastError();
