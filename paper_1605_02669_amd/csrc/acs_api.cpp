@@ -119,15 +119,18 @@ Layout make_layout(int n, int m, int cl, int ldn, int memory, int s, int mode) {
     L.upd_head = take(sizeof(int32_t) * (size_t)n);
   }
   if (mode == ACS_SYNC) {
-    // the barrier's words: a line per 16 ants, the place of a dense handle's
-    // lists where they need more (up to 1200 ants), a larger region where
-    // that is too small as well
+    // the barrier's words: a line per 16 ants and, where they need more (up to 1200
+    // ants), the place of a dense handle's lists or, where that is too small as well,
+    // of its eta^beta table: nothing reads either once the handle is built.  (With the
+    // selective memory both are read, and the region is larger.)
     const size_t words = sizeof(uint32_t) * acs::sync_barrier_words(m);
     const size_t lines = 128 * (size_t)(((int64_t)m + 15) / 16 + 1);
-    const bool in_cand =
-        words > lines && memory == ACS_DENSE && words <= sizeof(int32_t) * (size_t)n * cl;
-    L.bflags = take(in_cand ? lines : std::max(lines, words));
-    if (in_cand) L.bflags = L.cand;
+    const size_t place = words <= lines || memory != ACS_DENSE          ? 0
+                         : words <= sizeof(int32_t) * (size_t)n * cl    ? L.cand
+                         : words <= sizeof(float) * (size_t)kEtaEntries ? L.eta
+                                                                        : 0;
+    L.bflags = take(place ? lines : std::max(lines, words));
+    if (place) L.bflags = place;
   }
   if (memory == ACS_DENSE) {
     L.tours = take(tour_bytes);

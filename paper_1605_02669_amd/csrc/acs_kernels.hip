@@ -938,7 +938,6 @@ __global__ __launch_bounds__(256) void k_fill(Dev D, float tau0, uint32_t dmax, 
     D.spm_tail[e] = (uint32_t)(D.spm_s - 1);
     D.upd_head[e] = -1;
   }
-  if (D.bflags && e < (size_t)D.nbflags) D.bflags[e] = 0u;
   if (D.ccnt && e < (size_t)D.n * D.cl) D.ccnt[e] = 0u;
   if (e == 0) {
     D.gstate[0] = -1;
@@ -1579,7 +1578,8 @@ __global__ __launch_bounds__(1024) void k_construct_sync_lds(Dev D, Iter A) {
 }
 
 // The grid barrier's words before an iteration in which they are due (see
-// barrier_reached).
+// barrier_reached): the first one, then every kBarrierClear-th.  (When the handle
+// is built their place may still hold the eta^beta table.)
 __global__ __launch_bounds__(256) void k_barrier_clear(Dev D, uint32_t it) {
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e < D.nbflags) D.bflags[e] = barrier_epoch(it, 0);
@@ -2553,7 +2553,7 @@ __device__ __forceinline__ uint32_t grp_read(uint32_t v, int base, int k) {
 }
 
 // Many ants per SIMD are in flight, so the instructions of a step set the time
-// (256 instances, n in [100, 2000], m = n: 20.8 -> 16.2 ms per
+// (256 instances, n in [100, 2000], m = n: 20.8 -> 16.3 ms per
 // construction).  The records come by buffer loads (32-bit offsets; pointers read from
 // memory are generic to the compiler and become flat accesses, which also
 // hold up LDS), an entry's address is computed only where it is updated, the
@@ -4463,7 +4463,7 @@ hipError_t launch_fill(const Dev &d, float tau0, uint32_t dmax, bool eta_falls, 
   size_t total = d.tau ? (size_t)d.n * d.ldn : (size_t)d.n;
   if (d.fpre) total = std::max(total, (size_t)d.n * kFpre);
   if (d.spm) total = std::max(total, (size_t)d.n * d.spm_s);
-  total = std::max(std::max(total, (size_t)8), (size_t)d.nbflags);
+  total = std::max(total, (size_t)8);
   hipLaunchKernelGGL(k_fill, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, d, tau0, dmax,
                      eta_falls ? 1 : 0);
   return hipGetLastError();
